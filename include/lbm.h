@@ -628,8 +628,8 @@ lbm_status lbm3d_create(const lbm3d_grid* grid, const lbm3d_sphere* spheres, int
                         lbm3d_ctx** out);
 
 /* Enqueue n time steps (one launch each, pressure planes included; free
- * spheres add a Newton-Euler launch, moving spheres an owner-map and a
- * refill launch; plus one launch for the last step's force totals).
+ * spheres add a Newton-Euler launch, moving spheres a geometry and refill
+ * launch; plus one launch for the last step's force totals).
  * Asynchronous. */
 lbm_status lbm3d_step(lbm3d_ctx* ctx, int64_t n);
 

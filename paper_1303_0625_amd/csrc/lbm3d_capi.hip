@@ -532,7 +532,7 @@ lbm_status lbm3d_step(lbm3d_ctx* c, int64_t n) {
             const StepKernel kern = c->g.dtype == LBM_F64
                                         ? (nt ? step_kernel<double, true>(ibb, pr) : step_kernel<double, false>(ibb, pr))
                                         : (nt ? step_kernel<float, true>(ibb, pr) : step_kernel<float, false>(ibb, pr));
-            kern<<<grid, kBlock, 0, c->stream>>>(p, par, n_lead, a);
+            kern<<<grid, kBlock, c->L.nmovers > 0 ? 2 * kBoxLinks : 0, c->stream>>>(p, par, n_lead, a);
         }
         double* sol_n = at<double>(c, c->L.sol[par ^ 1]);
         if (c->nfree > 0) {
@@ -541,30 +541,26 @@ lbm_status lbm3d_step(lbm3d_ctx* c, int64_t n) {
             fa.sol_t = p.sol;
             fa.sol_n = sol_n;
             fa.mass = at<double>(c, c->L.mass);
-            fa.partial = p.partial + (size_t)(c->t & 1) * c->L.nchunks * 12;
-            // step t - 1's partials are intact until step t + 1 writes them
-            fa.partial_prev = (c->force_avg && c->t >= 1) ? p.partial + (size_t)((c->t - 1) & 1) * c->L.nchunks * 12
-                                                           : nullptr;
+            fa.partial = p.partial;
+            fa.average = c->force_avg;
             fa.solid_chunk0 = p.solid_chunk0;
             fa.err = at<int>(c, c->L.err);
             for (int d = 0; d < 3; ++d) fa.G[d] = c->G[d];
             fa.scheme = c->dyn_scheme == LBM_CME ? 0 : 1;
-            k3_free<<<1, kBlock, 0, c->stream>>>(fa, c->t, a);
+            k3_free<<<(unsigned)(c->ns + 1), 64, 0, c->stream>>>(fa, par, p.tctr, a);
         }
         if (c->L.nmovers > 0) {
             // geometry of step t + 1, then the newborn refill into the step's output
             uint8_t* own_n = at<uint8_t>(c, c->L.own[par ^ 1]);
-            const int64_t N = (int64_t)c->g.nx * c->g.ny * c->g.nz;
-            k3_raster<<<(unsigned)((N + kBlock - 1) / kBlock), kBlock, 0, c->stream>>>(sol_n, own_n, c->t + 1, a);
-            k3_flags<<<(unsigned)((N + kBlock - 1) / kBlock), kBlock, 0, c->stream>>>(
-                own_n, at<uint8_t>(c, c->L.flags[par ^ 1]), a);
-            const int cpm = (int)(((int64_t)c->L.box * c->L.box * c->L.box + kBlock - 1) / kBlock);
-            const unsigned nrb = (unsigned)(cpm * c->L.nmovers);
+            uint8_t* flags_n = at<uint8_t>(c, c->L.flags[par ^ 1]);
+            // tiles of 8 x 8 x 4 nodes: `tiles` along x and y, twice as many along z
+            const int tiles = (c->L.box + kTileX - 1) / kTileX;
+            const unsigned nb = (unsigned)(2 * tiles * tiles * tiles * c->L.nmovers);
             const int* mv = at<int>(c, c->L.movers);
             if (c->g.dtype == LBM_F64)
-                k3_refill<double><<<nrb, kBlock, 0, c->stream>>>(p, sol_n, own_n, mv, cpm, c->t, a);
+                k3_move<double><<<nb, kBlock, 0, c->stream>>>(p, sol_n, own_n, flags_n, mv, tiles, par, a);
             else
-                k3_refill<float><<<nrb, kBlock, 0, c->stream>>>(p, sol_n, own_n, mv, cpm, c->t, a);
+                k3_move<float><<<nb, kBlock, 0, c->stream>>>(p, sol_n, own_n, flags_n, mv, tiles, par, a);
         }
         if (timed) {
             HIPCHK3(c, hipEventRecord(c->ev[c->ev_used + 1], c->stream));
@@ -601,10 +597,12 @@ lbm_status lbm3d_force_history(lbm3d_ctx* c, int64_t first, int64_t count, doubl
         return LBM_ESTATE;
     }
     const size_t row = 8 * (size_t)(c->ns + 1) * 12;
-    for (int64_t k = 0; k < count; ++k) {
-        const size_t src = c->L.hist + row * (size_t)((first + k) % c->hist_cap);
-        HIPCHK3(c, hipMemcpyAsync((char*)d_out + row * (size_t)k, c->ws + src, row, hipMemcpyDeviceToDevice,
-                                  c->stream));
+    // one copy per contiguous run of the ring
+    for (int64_t k = 0; k < count;) {
+        const int64_t slot = (first + k) % c->hist_cap, run = std::min<int64_t>(count - k, c->hist_cap - slot);
+        HIPCHK3(c, hipMemcpyAsync((char*)d_out + row * (size_t)k, c->ws + c->L.hist + row * (size_t)slot,
+                                  row * (size_t)run, hipMemcpyDeviceToDevice, c->stream));
+        k += run;
     }
     return LBM_OK;
 }

@@ -213,16 +213,56 @@ struct Ptrs {
 // (e_i + v) b; torque r x F about the sphere's centre.
 // IBB: interpolated bounce-back may be on (a.ibb); without it the link code
 // (and the kernel's registers) stay those of half-way bounce-back.
+//
+// A moving sphere has no link list: a workgroup takes kChunk nodes of its scan
+// box, two neighbouring ones per thread, finds each node's links from nineteen
+// owner loads issued together, and writes the links in node order (a scan over
+// the workgroup) to `list` in LDS; the links are then evaluated one per
+// thread.  (One thread walking a node's eighteen directions in turn, each with
+// its own dependent loads and square root, took 80 us per step on a 150 x 42 x
+// 42 tube with a sphere of r = 5.9; the whole step launch takes 25 us now.)
+constexpr int kBoxLinks = kChunk * (kQ - 1);  // links of one chunk of box nodes
+
+// Sum of each of the twelve components over the wave: an exchange halves the
+// components a lane carries while it doubles the lanes summed (lanes 0-31
+// keep components 0-5, then the lower 16 of each half three of them), so
+// 6 + 3 + 3 * 4 exchanges do what 12 * 6 did, adding the same pairs.  The
+// lanes 0, 16, 32 and 48 hold components 0-2, 3-5, 6-8 and 9-11.
+__device__ inline void wave_sum12(const double acc[12], double out[3]) {
+    const int lane = (int)threadIdx.x & 63;
+    const bool hi = (lane & 32) != 0, mid = (lane & 16) != 0;
+    double h[6];
+#pragma unroll
+    for (int q = 0; q < 6; ++q) {
+        const double keep = hi ? acc[6 + q] : acc[q], give = hi ? acc[q] : acc[6 + q];
+        h[q] = keep + __shfl_xor(give, 32, 64);
+    }
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        const double keep = mid ? h[3 + q] : h[q], give = mid ? h[q] : h[3 + q];
+        out[q] = keep + __shfl_xor(give, 16, 64);
+    }
+#pragma unroll
+    for (int off = 8; off >= 1; off >>= 1)
+#pragma unroll
+        for (int q = 0; q < 3; ++q) out[q] += __shfl_xor(out[q], off, 64);
+}
+
 template <typename T, bool IBB>
 __device__ inline void force_role3(int c, const Ptrs& p, double* __restrict__ partial, const Args& a,
-                                   double (*red)[12], int64_t t) {
+                                   double (*red)[12], uint16_t* __restrict__ list, int64_t t) {
     const T* f = (const T*)p.fin;
     const int s = p.chunk_solid[c];
     const int start = p.chunk_start[c];
-    // a moving sphere's links are found by scanning its box at step t (one
-    // node and its 18 directions per thread); other solids walk their list
     const bool box = s > 0 && p.sol[kSolidRow * s + 10] != 0.0;
     int bx0 = 0, by0 = 0, bz0 = 0;
+    int end = 0, first = start;
+    auto box_node = [&](int k, int& x, int& y, int& z) {
+        const int bx = k % a.box, by = (k / a.box) % a.box, bz = k / (a.box * a.box);
+        x = ((bx0 + bx) % a.nx + a.nx) % a.nx;
+        y = ((by0 + by) % a.ny + a.ny) % a.ny;
+        z = ((bz0 + bz) % a.nz + a.nz) % a.nz;
+    };
     if (box) {
         double X[3];
         centre3(p.sol, s, t, X);
@@ -230,23 +270,46 @@ __device__ inline void force_role3(int c, const Ptrs& p, double* __restrict__ pa
         bx0 = (int)floor(X[0] - r0) - 2;
         by0 = (int)floor(X[1] - r0) - 2;
         bz0 = (int)floor(X[2] - r0) - 2;
+        const int nbox = a.box * a.box * a.box;
+        uint32_t mask[2] = {0u, 0u};  // bit i: a link along i into the sphere
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            const int k = start + 2 * (int)threadIdx.x + r;
+            int x, y, z;
+            box_node(k < nbox ? k : 0, x, y, z);
+            const uint8_t self = p.own[((int64_t)z * a.ny + y) * a.pitch + x];
+            uint32_t m = 0;
+#pragma unroll
+            for (int i = 1; i < kQ; ++i) {
+                const int xb = wrap3(x + kE[i][0], a.nx), yb = wrap3(y + kE[i][1], a.ny), zb = wrap3(z + kE[i][2], a.nz);
+                m |= p.own[((int64_t)zb * a.ny + yb) * a.pitch + xb] == s ? 1u << i : 0u;
+            }
+            mask[r] = k < nbox && self == 0 ? m : 0u;
+        }
+        const int cnt = __builtin_popcount(mask[0]) + __builtin_popcount(mask[1]);
+        int total;
+        int off = lbm::block_scan<kBlock>(cnt, reinterpret_cast<int*>(red), total);
+#pragma unroll
+        for (int r = 0; r < 2; ++r)
+            for (uint32_t m = mask[r]; m != 0u; m &= m - 1u)
+                list[off++] = (uint16_t)((2 * threadIdx.x + (uint32_t)r) << 5 | (uint32_t)__builtin_ctz(m));
+        __syncthreads();
+        first = 0;
+        end = total;
+    } else {
+        const int n = p.seg_cnt[s];
+        end = start + kChunk < n ? start + kChunk : n;
     }
-    const int n = box ? a.box * a.box * a.box : p.seg_cnt[s];
-    const int end = start + kChunk < n ? start + kChunk : n;
     const uint32_t* L = p.links + p.seg_off[s];
     double acc[12];
 #pragma unroll
     for (int q = 0; q < 12; ++q) acc[q] = 0.0;
-    for (int k = start + (int)threadIdx.x; k < end; k += kBlock) {
-        int x, y, z, i0, i1;
+    for (int k = first + (int)threadIdx.x; k < end; k += kBlock) {
+        int x, y, z, i;
         if (box) {
-            const int bx = k % a.box, by = (k / a.box) % a.box, bz = k / (a.box * a.box);
-            x = ((bx0 + bx) % a.nx + a.nx) % a.nx;
-            y = ((by0 + by) % a.ny + a.ny) % a.ny;
-            z = ((bz0 + bz) % a.nz + a.nz) % a.nz;
-            if (p.own[((int64_t)z * a.ny + y) * a.pitch + x] != 0) continue;
-            i0 = 1;
-            i1 = kQ;
+            const uint32_t code = list[k];
+            box_node(start + (int)(code >> 5), x, y, z);
+            i = (int)(code & 31u);
         } else {
             const uint32_t code = L[k];
             const uint32_t node = code >> 5;
@@ -254,15 +317,9 @@ __device__ inline void force_role3(int c, const Ptrs& p, double* __restrict__ pa
             const uint32_t ln = node / (uint32_t)a.nx;  // z * ny + y
             y = (int)(ln % (uint32_t)a.ny);
             z = (int)(ln / (uint32_t)a.ny);
-            i0 = (int)(code & 31u);
-            i1 = i0 + 1;
+            i = (int)(code & 31u);
         }
         const int64_t line = (int64_t)z * a.ny + y;
-        for (int i = i0; i < i1; ++i) {
-        if (box) {
-            const int xb = wrap3(x + kE[i][0], a.nx), yb = wrap3(y + kE[i][1], a.ny), zb = wrap3(z + kE[i][2], a.nz);
-            if (p.own[((int64_t)zb * a.ny + yb) * a.pitch + xb] != s) continue;
-        }
         const double ex = kE[i][0], ey = kE[i][1], ez = kE[i][2], w = w3(i);
         // surface point x_f + q e_i (q = 1/2 unless interpolated on a sphere)
         double q = 0.5;
@@ -306,16 +363,13 @@ __device__ inline void force_role3(int c, const Ptrs& p, double* __restrict__ pa
             acc[10] += r[2] * Fg[0] - r[0] * Fg[2];
             acc[11] += r[0] * Fg[1] - r[1] * Fg[0];
         }
-        }
     }
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    double tot[3];
+    wave_sum12(acc, tot);
+    if ((lane & 15) == 0)
 #pragma unroll
-    for (int q = 0; q < 12; ++q) {
-        double v = acc[q];
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-        if (lane == 0) red[wv][q] = v;
-    }
+        for (int q = 0; q < 3; ++q) red[wv][3 * (lane >> 4) + q] = tot[q];
     __syncthreads();
     if (threadIdx.x < 12) {
         const int q = threadIdx.x;
@@ -503,11 +557,12 @@ __device__ inline void update3(int xo, int y, int z, const Ptrs& p, const Args& 
 template <typename T, bool NT, bool IBB, bool PR>
 __global__ __launch_bounds__(kBlock) void k3_step(Ptrs p, int parity, int n_lead, Args a) {
     __shared__ double red[kBlock / 64][12];
+    extern __shared__ uint16_t box_links[];  // kBoxLinks entries when a sphere moves
     const int b = (int)blockIdx.x;
     if (b < n_lead) {
         const int64_t t = p.tctr[parity];
         if (b < a.nchunks) {
-            force_role3<T, IBB>(b, p, p.partial + (size_t)(t & 1) * a.nchunks * 12, a, red, t);
+            force_role3<T, IBB>(b, p, p.partial + (size_t)(t & 1) * a.nchunks * 12, a, red, box_links, t);
         } else if (b < a.nchunks + (a.ns + 1) * 12) {
             const int pair = b - a.nchunks;
             if (t >= 1)
@@ -554,36 +609,6 @@ __device__ inline uint8_t owner3(const double* __restrict__ sol, int x, int y, i
     return o;
 }
 
-// Geometry of step t + 1 (moving spheres): the owner of every node.
-__global__ __launch_bounds__(kBlock) void k3_raster(const double* __restrict__ sol, uint8_t* __restrict__ own_n,
-                                                    int64_t t1, Args a) {
-    const int64_t n = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (n >= (int64_t)a.nx * a.ny * a.nz) return;
-    const int x = (int)(n % a.nx);
-    const int64_t line = n / a.nx;
-    own_n[line * a.pitch + x] = owner3(sol, x, (int)(line % a.ny), (int)(line / a.ny), t1, a);
-}
-
-// Flags of every node from the owners of step t + 1 (moving spheres).
-__global__ __launch_bounds__(kBlock) void k3_flags(const uint8_t* __restrict__ own_n, uint8_t* __restrict__ flags_n,
-                                                   Args a) {
-    const int64_t n = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (n >= (int64_t)a.nx * a.ny * a.nz) return;
-    const int x = (int)(n % a.nx);
-    const int64_t line = n / a.nx;
-    const int y = (int)(line % a.ny), z = (int)(line / a.ny);
-    uint8_t f = 0;
-    if (own_n[line * a.pitch + x] != 0) {
-        f = kSolidNode;
-    } else {
-        for (int i = 1; i < kQ; ++i) {
-            const int xb = wrap3(x + kE[i][0], a.nx), yb = wrap3(y + kE[i][1], a.ny), zb = wrap3(z + kE[i][2], a.nz);
-            if (own_n[((int64_t)zb * a.ny + yb) * a.pitch + xb] != 0) f = kNearSolid;
-        }
-    }
-    flags_n[line * a.pitch + x] = f;
-}
-
 // Post-advection deviation of direction j at node (x, y, z) from step t's
 // post-collision populations: streamed from x - e_j, or the half-way
 // bounce-back with the moving-wall term when that node is solid at t.
@@ -616,80 +641,144 @@ __device__ inline double pull3(const T* __restrict__ fin, const uint8_t* __restr
            6.0 * w3(j) * a.rho0 * (kE[j][0] * v[0] + kE[j][1] * v[1] + kE[j][2] * v[2]);
 }
 
-// Newborn refill (moving sphere `s`, one box node per thread, box around its
-// centre at t + 1): a node solid at t and fluid at t + 1 takes the average
-// over participating directions k (x + e_k old fluid: fluid at t and t + 1)
-// of A1/A2/A3 along k of the post-advection values (falling back A1 -> A2 ->
-// A3), or the equilibrium at its surface velocity when none takes part; then
-// it is collided and stored with the step's output.
+// Moving spheres after the step: geometry of step t + 1 and newborn refill, one
+// workgroup per tile of a moving sphere's box (edge a.box, around its centre at
+// t + 1), one node per thread.  The box holds every node whose owner or flag
+// can differ from those of step t - 1, which the maps of t + 1's parity still
+// hold: a sphere moves at most one node in two steps, its nodes stay within
+// floor(X - r) - 1 .. floor(X - r) + 2 ceil(r) + 1 and their neighbours one
+// further.  The owners at t + 1 of the tile and one node around it come from the
+// predicate that builds them (LDS), so no workgroup waits on another; where two
+// boxes overlap both write the same values.
+//
+// A newborn node (solid at t, fluid at t + 1) takes the average over
+// participating directions k (x + e_k old fluid: fluid at t and t + 1) of
+// A1/A2/A3 along k of the post-advection values (falling back A1 -> A2 -> A3),
+// or the equilibrium at its surface velocity when none takes part; then it is
+// collided and stored with the step's output.  The workgroup refills its
+// newborn nodes one after another, the 18 x 3 x 19 stencil values of a node in
+// parallel.  (Bound by latency: one thread walking a node's whole stencil took
+// 203 us, and rasters and flags of the whole lattice 12 us, on a 150 x 42 x 42
+// tube with one sphere of r = 5.9; this kernel takes 15 us.)
+constexpr int kTileX = 8, kTileY = 8, kTileZ = 4;
+static_assert(kTileX * kTileY * kTileZ == kBlock, "one node per thread");
+
 template <typename T>
-__global__ __launch_bounds__(kBlock) void k3_refill(Ptrs p, const double* __restrict__ sol_n,
-                                                    const uint8_t* __restrict__ own_n, const int* __restrict__ movers,
-                                                    int chunks_per_mover, int64_t t, Args a) {
-    const int m = (int)blockIdx.x / chunks_per_mover;
-    const int k0 = ((int)blockIdx.x % chunks_per_mover) * kBlock + (int)threadIdx.x;
-    if (k0 >= a.box * a.box * a.box) return;
+__global__ __launch_bounds__(kBlock) void k3_move(Ptrs p, const double* __restrict__ sol_n,
+                                                  uint8_t* __restrict__ own_n, uint8_t* __restrict__ flags_n,
+                                                  const int* __restrict__ movers, int tiles, int parity, Args a) {
+    constexpr int HX = kTileX + 2, HY = kTileY + 2, HZ = kTileZ + 2;
+    __shared__ uint8_t on[HZ * HY * HX];
+    __shared__ int born[kBlock];
+    __shared__ int n_born;
+    __shared__ int8_t use[kQ];
+    __shared__ double val[kQ][3][kQ];
+    __shared__ double out[kQ];
+    const int tid = (int)threadIdx.x;
+    const int m = (int)blockIdx.x / (tiles * tiles * 2 * tiles);
+    int tile = (int)blockIdx.x - m * (tiles * tiles * 2 * tiles);
     const int s = movers[m];
+    const int64_t t = p.tctr[parity];
     double X[3];
     centre3(sol_n, s, t + 1, X);
     const double r0 = p.sol[kSolidRow * s + 3];
-    const int x = (((int)floor(X[0] - r0) - 2 + k0 % a.box) % a.nx + a.nx) % a.nx;
-    const int y = (((int)floor(X[1] - r0) - 2 + (k0 / a.box) % a.box) % a.ny + a.ny) % a.ny;
-    const int z = (((int)floor(X[2] - r0) - 2 + k0 / (a.box * a.box)) % a.nz + a.nz) % a.nz;
-    const int64_t line = (int64_t)z * a.ny + y;
-    if (p.own[line * a.pitch + x] != s || own_n[line * a.pitch + x] != 0) return;
-    const T* fin = (const T*)p.fin;
-    double acc[kQ];
+    const int tx = tile % tiles * kTileX, ty = tile / tiles % tiles * kTileY, tz = tile / (tiles * tiles) * kTileZ;
+    const int x0 = (int)floor(X[0] - r0) - 2 + tx, y0 = (int)floor(X[1] - r0) - 2 + ty,
+              z0 = (int)floor(X[2] - r0) - 2 + tz;
+    auto wrapn = [](int v, int n) { return (v % n + n) % n; };
+    if (tid == 0) n_born = 0;
+    for (int q = tid; q < HZ * HY * HX; q += kBlock)
+        on[q] = owner3(sol_n, wrapn(x0 + q % HX - 1, a.nx), wrapn(y0 + q / HX % HY - 1, a.ny),
+                       wrapn(z0 + q / (HX * HY) - 1, a.nz), t + 1, a);
+    const int lx = tid % kTileX, ly = tid / kTileX % kTileY, lz = tid / (kTileX * kTileY);
+    const int x = wrapn(x0 + lx, a.nx), y = wrapn(y0 + ly, a.ny), z = wrapn(z0 + lz, a.nz);
+    const int64_t at = ((int64_t)z * a.ny + y) * a.pitch + x;
+    const bool in_box = tx + lx < a.box && ty + ly < a.box && tz + lz < a.box;
+    const uint8_t was = p.own[at];
+    __syncthreads();
+    if (in_box) {
+        const int q = ((lz + 1) * HY + ly + 1) * HX + lx + 1;
+        const uint8_t o = on[q];
+        uint8_t fl = o != 0 ? kSolidNode : 0;
+        if (o == 0) {
 #pragma unroll
-    for (int j = 0; j < kQ; ++j) acc[j] = 0.0;
-    int np = 0;
-    for (int k = 1; k < kQ; ++k) {
-        int qx[4], qy[4], qz[4];
-        bool old[4] = {false, false, false, false};
-        for (int mm = 1; mm <= 3; ++mm) {
-            qx[mm] = wrap3(x + mm * kE[k][0], a.nx);
-            qy[mm] = wrap3(y + mm * kE[k][1], a.ny);
-            qz[mm] = wrap3(z + mm * kE[k][2], a.nz);
-            // x + m e_k for m <= 3 stays within one period (n >= 4)
-            const int64_t q = ((int64_t)qz[mm] * a.ny + qy[mm]) * a.pitch + qx[mm];
-            old[mm] = p.own[q] == 0 && own_n[q] == 0;
-            if (!old[mm]) break;
+            for (int i = 1; i < kQ; ++i)
+                if (on[q + (kE[i][2] * HY + kE[i][1]) * HX + kE[i][0]] != 0) fl = kNearSolid;
         }
-        if (!old[1]) continue;
-        int scheme = a.refill;
-        if (scheme == 0 && !(old[2] && old[3])) scheme = 1;
-        if (scheme == 1 && !old[2]) scheme = 2;
-        ++np;
-        for (int j = 0; j < kQ; ++j) {
-            const double f1 = pull3<T>(fin, p.own, p.sol, qx[1], qy[1], qz[1], j, t, a);
-            double v = f1;
-            if (scheme <= 1) {
-                const double f2 = pull3<T>(fin, p.own, p.sol, qx[2], qy[2], qz[2], j, t, a);
-                if (scheme == 1) {
-                    v = 2.0 * f1 - f2;
-                } else {
-                    const double f3 = pull3<T>(fin, p.own, p.sol, qx[3], qy[3], qz[3], j, t, a);
-                    v = 3.0 * f1 - 3.0 * f2 + f3;
-                }
+        own_n[at] = o;
+        flags_n[at] = fl;
+        // (the order of the list affects no value: each node has its own)
+        if (was == s && o == 0) born[atomicAdd(&n_born, 1)] = tid;
+    }
+    __syncthreads();
+    const T* fin = (const T*)p.fin;
+    const int nb = n_born;
+    for (int b = 0; b < nb; ++b) {
+        const int id = born[b];
+        const int bx = wrapn(x0 + id % kTileX, a.nx), by = wrapn(y0 + id / kTileX % kTileY, a.ny),
+                  bz = wrapn(z0 + id / (kTileX * kTileY), a.nz);
+        // x + m e_k for m <= 3 stays within one period (n >= 4)
+        if (tid >= 1 && tid < kQ) {
+            bool old[4] = {false, true, true, true};
+            for (int mm = 1; mm <= 3; ++mm) {
+                const int qx = wrap3(bx + mm * kE[tid][0], a.nx), qy = wrap3(by + mm * kE[tid][1], a.ny),
+                          qz = wrap3(bz + mm * kE[tid][2], a.nz);
+                old[mm] = p.own[((int64_t)qz * a.ny + qy) * a.pitch + qx] == 0 && owner3(sol_n, qx, qy, qz, t + 1, a) == 0;
             }
-            acc[j] += v;
+            int scheme = -1;
+            if (old[1]) {
+                scheme = a.refill;
+                if (scheme == 0 && !(old[2] && old[3])) scheme = 1;
+                if (scheme == 1 && !old[2]) scheme = 2;
+            }
+            use[tid] = (int8_t)scheme;
         }
-    }
-    double d[kQ];
-    if (np > 0) {
-        for (int j = 0; j < kQ; ++j) d[j] = acc[j] / np;
-    } else {
-        double v[3], r[3];
-        surface_vel(sol_n, s, t + 1, x, y, z, a, v, r);
-        const double uu = v[0] * v[0] + v[1] * v[1] + v[2] * v[2];
-        for (int j = 0; j < kQ; ++j) {
-            const double eu = kE[j][0] * v[0] + kE[j][1] * v[1] + kE[j][2] * v[2];
-            d[j] = w3(j) * a.rho0 * (3.0 * eu + 4.5 * eu * eu - 1.5 * uu);
+        __syncthreads();
+        for (int w = tid; w < (kQ - 1) * 3 * kQ; w += kBlock) {
+            const int k = w / (3 * kQ) + 1, mm = w % (3 * kQ) / kQ + 1, j = w % kQ;
+            const int sc = use[k];
+            if (sc < 0 || mm > 3 - sc) continue;  // A1 takes three nodes, A2 two, A3 one
+            val[k][mm - 1][j] = pull3<T>(fin, p.own, p.sol, wrap3(bx + mm * kE[k][0], a.nx),
+                                         wrap3(by + mm * kE[k][1], a.ny), wrap3(bz + mm * kE[k][2], a.nz), j, t, a);
         }
+        __syncthreads();
+        if (tid < kQ) {
+            double acc = 0.0;
+            int np = 0;
+            for (int k = 1; k < kQ; ++k) {
+                const int sc = use[k];
+                if (sc < 0) continue;
+                ++np;
+                double v = val[k][0][tid];
+                if (sc == 1)
+                    v = 2.0 * v - val[k][1][tid];
+                else if (sc == 0)
+                    v = 3.0 * v - 3.0 * val[k][1][tid] + val[k][2][tid];
+                acc += v;
+            }
+            if (np > 0) {
+                out[tid] = acc / np;
+            } else {
+                double v[3], r[3];
+                surface_vel(sol_n, s, t + 1, bx, by, bz, a, v, r);
+                const double uu = v[0] * v[0] + v[1] * v[1] + v[2] * v[2];
+                const double eu = kE[tid][0] * v[0] + kE[tid][1] * v[1] + kE[tid][2] * v[2];
+                out[tid] = w3(tid) * a.rho0 * (3.0 * eu + 4.5 * eu * eu - 1.5 * uu);
+            }
+        }
+        __syncthreads();
+        if (tid == 0) {
+            double d[kQ];
+#pragma unroll
+            for (int j = 0; j < kQ; ++j) d[j] = out[j];
+            collide3(d, a);
+#pragma unroll
+            for (int j = 0; j < kQ; ++j) out[j] = d[j];
+        }
+        __syncthreads();
+        if (tid < kQ)
+            ((T*)p.fout)[(((int64_t)bz * a.ny + by) * kQ + tid) * a.pitch + bx] = Sto<T>::st(out[tid]);
     }
-    collide3(d, a);
-    T* fout = (T*)p.fout;
-    for (int j = 0; j < kQ; ++j) fout[(line * kQ + j) * a.pitch + x] = Sto<T>::st(d[j]);
 }
 
 // Totals of the last step tctr[parity] - 1 after a run of steps, one
@@ -705,9 +794,9 @@ __global__ __launch_bounds__(kBlock) void k3_finalize(const double* __restrict__
               red);
 }
 
-// Free spheres after step t (one thread per solid slot): the step's force
-// and torque of the chosen scheme, summed over the sphere's chunks in order,
-// drive the explicit Newton-Euler step V' = V + (F + (M - rho0 Vol) G)/M,
+// Free spheres after step t (one wave per solid slot): the step's force
+// and torque of the chosen scheme, summed over the sphere's chunks (lane l takes
+// chunks l, l + 64, ... in order, then a fixed tree), drive the explicit Newton-Euler step V' = V + (F + (M - rho0 Vol) G)/M,
 // Omega' = Omega + T/I, X' = X + V' into the next parity's table; every
 // other row is copied.  A free sphere that comes within 2 nodes of the duct
 // or another sphere, or moves more than half a node, sets bit 1 of err.
@@ -715,62 +804,86 @@ struct FreeArgs3 {
     const double* sol_t;
     double* sol_n;
     const double* mass;       // [ns + 1][4]: M, I, Vol
-    const double* partial;    // step t's chunk partials
-    const double* partial_prev;  // step t - 1's (force average), or nullptr
+    const double* partial;    // [2][nchunks][12] chunk partials, by step parity
+    int average;              // mean of the forces of steps t - 1 and t
     const int* solid_chunk0;
     int* err;
     double G[3];
     int scheme;               // 0 CME, 1 GME
 };
 
-__global__ __launch_bounds__(kBlock) void k3_free(FreeArgs3 fa, int64_t t, Args a) {
-    const int s = (int)threadIdx.x;
-    if (s > a.ns) return;
+__global__ __launch_bounds__(64) void k3_free(FreeArgs3 fa, int parity, const int64_t* __restrict__ tctr, Args a) {
+    const int s = (int)blockIdx.x, lane = (int)threadIdx.x;
     const double* S = fa.sol_t + kSolidRow * s;
     double* N = fa.sol_n + kSolidRow * s;
     if (s == 0 || S[11] == 0.0) {
-        for (int q = 0; q < kSolidRow; ++q) N[q] = S[q];
+        if (lane < kSolidRow) N[lane] = S[lane];
         return;
     }
-    // with the two-step average: the mean of the totals of steps t - 1 and t
-    double F[6];
-    for (int q = 0; q < 6; ++q) {
-        double v = 0.0;
-        for (int cc = fa.solid_chunk0[s]; cc < fa.solid_chunk0[s + 1]; ++cc) v += fa.partial[cc * 12 + 6 * fa.scheme + q];
-        if (fa.partial_prev) {
-            double w = 0.0;
-            for (int cc = fa.solid_chunk0[s]; cc < fa.solid_chunk0[s + 1]; ++cc)
-                w += fa.partial_prev[cc * 12 + 6 * fa.scheme + q];
-            v = 0.5 * (v + w);
+    const int64_t t = tctr[parity];
+    // partials of steps t and t - 1 (t - 1's are intact until step t + 1 writes them)
+    const double* cur = fa.partial + (size_t)(t & 1) * a.nchunks * 12;
+    const double* prev = fa.partial + (size_t)((t + 1) & 1) * a.nchunks * 12;
+    const bool average = fa.average && t >= 1;
+    double F[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0}, Fp[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    for (int cc = fa.solid_chunk0[s] + lane; cc < fa.solid_chunk0[s + 1]; cc += 64) {
+#pragma unroll
+        for (int q = 0; q < 6; ++q) F[q] += cur[cc * 12 + 6 * fa.scheme + q];
+        if (average) {
+#pragma unroll
+            for (int q = 0; q < 6; ++q) Fp[q] += prev[cc * 12 + 6 * fa.scheme + q];
         }
-        F[q] = v;
+    }
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1)
+#pragma unroll
+        for (int q = 0; q < 6; ++q) {
+            F[q] += __shfl_xor(F[q], off, 64);
+            if (average) Fp[q] += __shfl_xor(Fp[q], off, 64);
+        }
+    // with the two-step average: the mean of the totals of steps t - 1 and t
+    if (average) {
+#pragma unroll
+        for (int q = 0; q < 6; ++q) F[q] = 0.5 * (F[q] + Fp[q]);
     }
     const double M = fa.mass[4 * s], I = fa.mass[4 * s + 1], Vol = fa.mass[4 * s + 2];
     const double ext = M - a.rho0 * Vol;
-    for (int q = 0; q < kSolidRow; ++q) N[q] = S[q];
-    double speed2 = 0.0;
+    double nx[3], nv[3], no[3], speed2 = 0.0;
+#pragma unroll
     for (int d = 0; d < 3; ++d) {
-        N[4 + d] = S[4 + d] + (F[d] + ext * fa.G[d]) / M;
-        N[7 + d] = S[7 + d] + F[3 + d] / I;
-        N[d] = S[d] + N[4 + d];
-        speed2 += N[4 + d] * N[4 + d];
+        nv[d] = S[4 + d] + (F[d] + ext * fa.G[d]) / M;
+        no[d] = S[7 + d] + F[3 + d] / I;
+        nx[d] = S[d] + nv[d];
+        speed2 += nv[d] * nv[d];
     }
-    bool bad = speed2 > 0.25;
     const double r = S[3];
-    if (a.duct == 1) {
-        const double dy = N[1] - 0.5 * (a.ny - 1), dz = N[2] - 0.5 * (a.nz - 1);
-        bad |= sqrt(dy * dy + dz * dz) + r > a.R - 2.0;
-    } else if (a.duct == 2) {
-        bad |= N[2] - r < 2.0 || N[2] + r > a.nz - 3.0;
+    bool bad = speed2 > 0.25;
+    if (lane == 0) {
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            N[d] = nx[d];
+            N[4 + d] = nv[d];
+            N[7 + d] = no[d];
+        }
+        N[3] = r;
+        N[10] = S[10];
+        N[11] = S[11];
+        if (a.duct == 1) {
+            const double dy = nx[1] - 0.5 * (a.ny - 1), dz = nx[2] - 0.5 * (a.nz - 1);
+            bad |= sqrt(dy * dy + dz * dz) + r > a.R - 2.0;
+        } else if (a.duct == 2) {
+            bad |= nx[2] - r < 2.0 || nx[2] + r > a.nz - 3.0;
+        }
     }
-    for (int j = 1; j <= a.ns; ++j) {
+    for (int j = 1 + lane; j <= a.ns; j += 64) {
         if (j == s) continue;
         double Y[3];
         centre3(fa.sol_t, j, t, Y);  // the other sphere at step t (good to a node)
         double d2 = 0.0;
         const int n3[3] = {a.nx, a.ny, a.nz};
+#pragma unroll
         for (int d = 0; d < 3; ++d) {
-            const double dd = min_image3(N[d] - Y[d], n3[d]);
+            const double dd = min_image3(nx[d] - Y[d], n3[d]);
             d2 += dd * dd;
         }
         bad |= sqrt(d2) < r + fa.sol_t[kSolidRow * j + 3] + 2.0;

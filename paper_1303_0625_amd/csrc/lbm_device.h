@@ -410,6 +410,32 @@ __device__ inline void solid_range(const SolidDev& s, double X, double Y, int ma
     y1 = (long)ceil(Y + hy) + margin;
 }
 
+// Workgroup-wide exclusive scan of one int per thread (B threads): an
+// inclusive scan inside each wavefront by shuffles, then the wave totals
+// through LDS (two barriers; sh needs B / 64 ints).
+template <int B>
+__device__ inline int block_scan(int v, int* sh, int& total) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int x = v;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int y = __shfl_up(x, off, 64);
+        if (lane >= off) x += y;
+    }
+    if (lane == 63) sh[wave] = x;
+    __syncthreads();
+    int pre = 0, tot = 0;
+#pragma unroll
+    for (int w = 0; w < B / 64; ++w) {
+        const int tw = sh[w];
+        pre += w < wave ? tw : 0;
+        tot += tw;
+    }
+    total = tot;
+    __syncthreads();  // sh may be reused by the caller
+    return pre + x - v;
+}
+
 // XCD-aware block order: the hardware hands consecutive workgroups to the 8
 // XCDs in turn; remap so that each XCD walks a contiguous band of tiles and
 // the halo lines shared by neighbouring tiles stay in one L2.

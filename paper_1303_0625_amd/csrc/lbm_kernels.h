@@ -880,31 +880,6 @@ __global__ void k_wall_links(uint32_t* __restrict__ links, int nx, int ny) {
     }
 }
 
-// Block-wide exclusive scan of one int per thread (kBlock threads): an
-// inclusive scan inside each wavefront by shuffles, then the wave totals
-// through LDS (two barriers; sh needs kBlock / 64 ints).
-__device__ inline int block_exclusive_scan(int v, int* sh, int& total) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    int x = v;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const int y = __shfl_up(x, off, 64);
-        if (lane >= off) x += y;
-    }
-    if (lane == 63) sh[wave] = x;
-    __syncthreads();
-    int pre = 0, tot = 0;
-#pragma unroll
-    for (int w = 0; w < kBlock / 64; ++w) {
-        const int tw = sh[w];
-        pre += w < wave ? tw : 0;
-        tot += tw;
-    }
-    total = tot;
-    __syncthreads();  // sh may be reused by the caller
-    return pre + x - v;
-}
-
 // Build the link list of solid s from owner map own over its bounding range
 // at step t.  Each thread takes a contiguous run of the range's nodes, so the
 // scan keeps row-major (y, x, i) order.
@@ -945,7 +920,7 @@ __device__ inline void build_links_block(const uint8_t* __restrict__ own, uint32
     int cnt = 0;
     for (long q = q0; q < q1; ++q) cnt += links_of(q, nullptr, 0);
     int total;
-    int off = block_exclusive_scan(cnt, sh, total);
+    int off = block_scan<kBlock>(cnt, sh, total);
     const int cap = seg_cap[s];
     uint32_t* L = links + seg_off[s];
     if (total <= cap) {
@@ -1204,7 +1179,7 @@ __device__ inline void move_role(int m, uint8_t* __restrict__ lds, MoveShared<T>
         int cnt = 0;
         for (int q = q0; q < q1; ++q) cnt += links_at(q, nullptr, 0);
         int total;
-        int off = block_exclusive_scan(cnt, sm.scan, total);
+        int off = block_scan<kBlock>(cnt, sm.scan, total);
         if (total <= cap) {
             uint32_t* L = links_n + soff;
             for (int q = q0; q < q1; ++q) off += links_at(q, L, off);

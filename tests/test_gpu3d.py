@@ -451,3 +451,25 @@ def test_ibb_tube_sphere_f32_drag(oracle_mod, lbm_mod):
         rel = np.abs(h[100:, 1, off] - oh[100:, 1, 0]).max() / np.abs(oh[100:, 1, 0]).max()
         _say(f"ibb f32 drag history rel err scheme {sch} = {rel:.3e}")
         assert rel <= 1e-5
+
+
+@pytest.mark.parametrize("shape,spheres,ibb", [
+    # a box of 7 nodes, less than one tile; many newborn nodes per step for its size
+    ((16, 14, 12), [dict(cx=6.3, cy=6.1, cz=5.7, r=1.0, v=(0.17, -0.16, 0.15))], False),
+    # the box (17) is the whole lattice along z and one node past two tiles
+    ((24, 20, 17), [dict(cx=11.2, cy=9.4, cz=8.3, r=5.6, v=(0.05, 0.06, -0.05), omega=(0.002, 0.0, 0.001))], True),
+    # two moving spheres whose boxes overlap, one across the periodic corner
+    ((30, 26, 24), [dict(cx=28.9, cy=25.2, cz=0.4, r=4.0, v=(0.05, 0.08, 0.06)),
+                    dict(cx=7.6, cy=25.0, cz=0.9, r=2.4, v=(0.06, 0.07, 0.05))], False)])
+def test_moving_sphere_box_tiles_f64(oracle_mod, lbm_mod, shape, spheres, ibb):
+    """The geometry, link search and refill of moving spheres by tiles of
+    their boxes: FP64 fields, owners and forces against the oracle where a box
+    is smaller than a tile, ends inside one, spans the lattice, or overlaps
+    another sphere's."""
+    c = dict(name="sphere_boxes", nx=shape[0], ny=shape[1], nz=shape[2], tau=0.8, u0=(0.02, -0.01, 0.0),
+             g=(1e-5, 0.0, 0.0), spheres=[dict(s, moves=True) for s in spheres])
+    lat, osim = run_pair(oracle_mod, lbm_mod, c, 40, ibb=ibb)
+    assert osim.error == 0
+    er, eu = field_err(lat, osim)
+    assert er <= 1e-12 and eu <= 1e-12
+    assert force_err(lat, osim) <= 1e-10
