@@ -90,7 +90,11 @@ __device__ inline void centre3(const double* __restrict__ sol, int s, int64_t t,
     for (int d = 0; d < 3; ++d) X[d] = mv ? S[d] + (double)t * S[4 + d] : S[d];
 }
 
-__device__ inline double min_image3(double d, int n) { return d - (double)n * floor(d / (double)n + 0.5); }
+// (a difference well inside the half period is its own image: floor gives 0)
+__device__ inline double min_image3(double d, int n) {
+    if (fabs(d) < 0.49 * (double)n) return d;
+    return d - (double)n * floor(d / (double)n + 0.5);
+}
 
 // Rigid surface velocity of solid slot s at point p at step t (duct at
 // rest), and the arm from the centre.
