@@ -335,10 +335,10 @@ __device__ inline void solid_pos(const SolidDev& s, int64_t t, double& X, double
 }
 
 // Whether integer point (x, y) lies inside solid s centred at (X, Y).
-__device__ inline bool solid_inside(const SolidDev& s, double X, double Y, long x, long y) {
+__device__ inline bool solid_inside(const SolidDev& s, double X, double Y, double x, double y) {
 #pragma clang fp contract(off)
-    double dx = (double)x - X;
-    double dy = (double)y - Y;
+    double dx = x - X;
+    double dy = y - Y;
     if (s.shape == 0) {
         double d2 = dx * dx;
         d2 = d2 + dy * dy;

@@ -845,7 +845,7 @@ __global__ __launch_bounds__(kBlock) void k_raster(uint8_t* __restrict__ own,
     const long W = x1 - x0 + 1, H = y1 - y0 + 1;
     for (long q = threadIdx.x; q < W * H; q += kBlock) {
         long yy = y0 + q / W, xx = x0 + q % W;
-        if (!solid_inside(S, X, Y, xx, yy)) continue;
+        if (!solid_inside(S, X, Y, (double)xx, (double)yy)) continue;
         if (g.walls && (yy < 0 || yy >= g.ny)) continue;
         own[(int64_t)wrapi(yy, g.ny) * g.opitch + wrapi(xx, g.nx)] = (uint8_t)s;
     }
@@ -1006,11 +1006,10 @@ template <typename T>
 struct MoveShared {
     using C = typename Sto<T>::C;
     SolidDev body;  // the mover's record (kept here rather than in registers)
-    int scan[kBlock];
-    int nb_count;
+    int nb_count;  // newborn nodes (part 1), links (part 0)
     int nb_list[kNewbornMax];
     int8_t nb_use[kNewbornBatch][8];  // -1: no participation, else 0/1/2
-    C nb_val[kNewbornBatch][8][3][9];
+    C nb_val[kNewbornBatch][8][3][9];  // (part 0: link counts per 64 box nodes)
     C nb_new[kNewbornBatch][9];
     C nb_mom[kNewbornBatch][4];
 };
@@ -1051,14 +1050,11 @@ __device__ inline void move_role(int m, uint8_t* __restrict__ lds, MoveShared<T>
     if (fr) {
         FreeDyn& D = fr->dyn[m - part * a.n_movers];
         const int k0 = (int)(t % 3), km = (int)((t + 2) % 3), kp = (int)((t + 1) % 3);
-        double F[3];
+        double F[3] = {0.0, 0.0, 0.0};
+        const int c1 = fr->solid_chunk0[s + 1];
+        for (int cc = fr->solid_chunk0[s]; cc < c1; ++cc)
 #pragma unroll
-        for (int q = 0; q < 3; ++q) {
-            double v = 0.0;
-            for (int cc = fr->solid_chunk0[s]; cc < fr->solid_chunk0[s + 1]; ++cc)
-                v += fr->partial[cc * 6 + 3 * fr->scheme + q];
-            F[q] = v;
-        }
+            for (int q = 0; q < 3; ++q) F[q] += fr->partial[cc * 6 + 3 * fr->scheme + q];
         const double ext = D.M - fr->rho0 * D.A;
         Vnx = D.Vx[k0] + (F[0] + ext * fr->Gx) / D.M;
         Vny = D.Vy[k0] + (F[1] + ext * fr->Gy) / D.M;
@@ -1095,94 +1091,161 @@ __device__ inline void move_role(int m, uint8_t* __restrict__ lds, MoveShared<T>
         if (threadIdx.x == 0) atomicOr(errflag, 4);
         return;
     }
-    auto gidx = [&](int q, int& gx, int& gy) -> bool {  // box index -> lattice node
-        long yy = y0 + q / W, xx = x0 + q % W;
-        if (a.walls && (yy < 0 || yy >= a.ny)) return false;
-        gx = wrapi(xx, a.nx);
-        gy = wrapi(yy, a.ny);
+    // Box node (qx, qy) is lattice node (bx + qx, by + qy) wrapped into the
+    // lattice: the box's corner is wrapped once (a 64-bit remainder per node and
+    // axis was most of the mover's time), and a box may be wider than the
+    // lattice, so the wrap repeats.
+    const int bx = wrapi(x0, a.nx);
+    const int by = a.walls ? (int)y0 : wrapi(y0, a.ny);
+    auto at_xy = [&](int qx, int qy, int& gx, int& gy) -> bool {
+        gx = bx + qx;
+        while (gx >= a.nx) gx -= a.nx;
+        gy = by + qy;
+        if (a.walls) return gy >= 0 && gy < a.ny;
+        while (gy >= a.ny) gy -= a.ny;
         return true;
     };
+    auto gidx = [&](int q, int& gx, int& gy) -> bool {
+        const int qy = q / W;
+        return at_xy(q - qy * W, qy, gx, gy);
+    };
+    // a thread walks the box nodes threadIdx.x, threadIdx.x + kBlock, ...: its
+    // column and row advance without a division per node
+    const int row0 = (int)threadIdx.x / W, col0 = (int)threadIdx.x - row0 * W;
+    const int drow = kBlock / W, dcol = kBlock - drow * W;
+    auto next_node = [&](int& qx, int& qy) {
+        qx += dcol;
+        qy += drow;
+        if (qx >= W) {
+            qx -= W;
+            ++qy;
+        }
+    };
     if (threadIdx.x == 0) sm.nb_count = 0;
-    // 1. stage the owner maps (part 0 needs only the second one); loads of
-    // a round are issued before any store
-    constexpr int R = 8;
-    for (int q0 = 0; q0 < N; q0 += R * kBlock) {
-        uint8_t vt[R], vn[R];
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const int q = q0 + r * kBlock + threadIdx.x;
-            int gx, gy;
-            vt[r] = vn[r] = kWallMark;
-            if (q < N && gidx(q, gx, gy)) {
-                const int64_t o = (int64_t)gy * a.opitch + gx;
-                if (part == 1) vt[r] = own_t[o];
-                vn[r] = own_n[o];
-            }
-        }
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const int q = q0 + r * kBlock + threadIdx.x;
-            if (q < N) {
-                ot[q] = vt[r];
-                on[q] = vn[r];
-            }
-        }
-    }
+    // 1. stage the owner maps (part 0 needs only the second one; the loads of a
+    // round are issued before any is used, so addresses outside the walls are
+    // clamped and the value replaced) and rasterise G_{t+1} on the way: the
+    // body at t+1, and what it left cleared.  Collect the newborn nodes (solid
+    // at t, fluid at t+1); their order in the list does not affect any value
     __syncthreads();
-    // 2. G_{t+1}: rasterise the body at t+1, clear what it left; collect the
-    // newborn nodes (solid at t, fluid at t+1); their order in the list does
-    // not affect any value
-    for (int q = threadIdx.x; q < N; q += kBlock) {
-        const long yy = y0 + q / W, xx = x0 + q % W;
-        const uint8_t v = on[q];
-        const bool in = solid_inside(S, Xn, Yn, xx, yy);
-        // a free body has no validated path: flag it meeting a wall or body
-        if (fr && in && (v == kWallMark || (v != 0 && v != s))) atomicOr(errflag, 8);
-        if (v == kWallMark) continue;
-        const uint8_t nv = in ? (uint8_t)s : (v == s ? (uint8_t)0 : v);
-        if (nv != v) {
-            on[q] = nv;
-            if (part == 0) {
+    {
+        constexpr int R = 4;
+        int qx = col0, qy = row0;
+        const double xd = (double)x0, yd = (double)y0;  // (exact sums: the node's integer coordinates)
+        for (int q0 = 0; q0 < N; q0 += R * kBlock) {
+            uint8_t vt[R], vn[R];
+            uint32_t o[R];
+            uint32_t outside = 0;
+            const int qx0 = qx, qy0 = qy;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
                 int gx, gy;
-                gidx(q, gx, gy);
-                own_n[(int64_t)gy * a.opitch + gx] = nv;
+                if (!at_xy(qx, qy, gx, gy)) outside |= 1u << r;
+                gy = gy < 0 ? 0 : (gy < a.ny ? gy : a.ny - 1);
+                o[r] = (uint32_t)gy * (uint32_t)a.opitch + (uint32_t)gx;
+                next_node(qx, qy);
             }
-        }
-        if (part == 1 && ot[q] == s && nv == 0) {
-            const int k = atomicAdd(&sm.nb_count, 1);
-            if (k < kNewbornMax) sm.nb_list[k] = q;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                vn[r] = own_n[o[r]];
+                vt[r] = part == 1 ? own_t[o[r]] : kWallMark;
+            }
+            qx = qx0;
+            qy = qy0;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const int q = q0 + r * kBlock + (int)threadIdx.x;
+                const bool wall = (outside >> r & 1u) != 0u;
+                const uint8_t v = wall ? kWallMark : vn[r], ov = wall ? kWallMark : vt[r];
+                const bool in = solid_inside(S, Xn, Yn, xd + (double)qx, yd + (double)qy);
+                if (q < N) {
+                    // a free body has no validated path: flag it meeting a wall or body
+                    if (fr && in && (v == kWallMark || (v != 0 && v != s))) atomicOr(errflag, 8);
+                    const uint8_t nv = wall ? v : (in ? (uint8_t)s : (v == s ? (uint8_t)0 : v));
+                    on[q] = nv;
+                    if (part == 0) {
+                        if (nv != v) own_n[o[r]] = nv;
+                    } else {
+                        ot[q] = ov;
+                        if (ov == s && nv == 0) {
+                            const int k = atomicAdd(&sm.nb_count, 1);
+                            if (k < kNewbornMax) sm.nb_list[k] = q;
+                        }
+                    }
+                }
+                next_node(qx, qy);
+            }
         }
     }
     __syncthreads();
-    // 3. link list of G_{t+1}, row-major (y, x, i) over the box interior
+    // 3. link list of G_{t+1}, row-major (y, x, i) over the box interior.  Wave w
+    // takes the groups of 64 consecutive nodes w, w + 4, ...: each lane marks
+    // its node's directions into the body as bits (kept in place of the owners
+    // of G_t, which part 0 does not stage); a link's place is the number of
+    // links in the groups before, plus that of the lanes before in its own
+    // (the ballots of the eight bits).  No thread walks a run of nodes: with a
+    // contiguous run per thread this phase took 10 to 16 us of the mover's 13
+    // to 23 (discs of r = 9 to 15), now 4 to 5.
     if (part == 0) {
-        const int chunk = (N + kBlock - 1) / kBlock;
-        const int q0 = threadIdx.x * chunk;
-        const int q1 = q0 + chunk < N ? q0 + chunk : N;
-        auto links_at = [&](int q, uint32_t* out, int base) -> int {
-            const int qx = q % W, qy = q / W;
-            if (qx == 0 || qy == 0 || qx == W - 1 || qy == H - 1 || on[q] != 0) return 0;
-            int c = 0;
+        int* gtot = reinterpret_cast<int*>(&sm.nb_val[0][0][0][0]);  // links per group, then before it
+        const int lane = (int)threadIdx.x & 63;
+        const int ngrp = (N + 63) / 64;
+        {
+            int qx = col0, qy = row0;
+            for (int q = threadIdx.x; q - lane < N; q += kBlock, next_node(qx, qy)) {
+                uint32_t bits = 0;
+                if (q < N && qx != 0 && qy != 0 && qx != W - 1 && qy != H - 1) {
+                    uint8_t nb[8];
 #pragma unroll
-            for (int i = 1; i < 9; ++i) {
-                if (on[q + ey_(i) * W + ex_(i)] == s) {
-                    if (out) {
-                        int gx, gy;
-                        gidx(q, gx, gy);
-                        out[base + c] = ((uint32_t)gy * (uint32_t)a.nx + (uint32_t)gx) << 4 | (uint32_t)i;
-                    }
-                    ++c;
+                    for (int i = 1; i < 9; ++i) nb[i - 1] = on[q + ey_(i) * W + ex_(i)];
+                    const uint8_t self = on[q];
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) bits |= nb[i] == s ? 1u << i : 0u;
+                    bits = self == 0 ? bits : 0u;
                 }
+                if (q < N) ot[q] = (uint8_t)bits;
+                int c = 0;
+#pragma unroll
+                for (int i = 0; i < 8; ++i) c += __builtin_popcountll(__ballot((bits >> i & 1u) != 0u));
+                if (lane == 0) gtot[q >> 6] = c;
             }
-            return c;
-        };
-        int cnt = 0;
-        for (int q = q0; q < q1; ++q) cnt += links_at(q, nullptr, 0);
-        int total;
-        int off = block_scan<kBlock>(cnt, sm.scan, total);
+        }
+        __syncthreads();
+        if (threadIdx.x < 64) {
+            int carry = 0;
+            for (int g0 = 0; g0 < ngrp; g0 += 64) {
+                const int v = g0 + lane < ngrp ? gtot[g0 + lane] : 0;
+                int x = v;
+#pragma unroll
+                for (int off = 1; off < 64; off <<= 1) {
+                    const int y = __shfl_up(x, off, 64);
+                    if (lane >= off) x += y;
+                }
+                if (g0 + lane < ngrp) gtot[g0 + lane] = carry + x - v;
+                carry += __shfl(x, 63, 64);
+            }
+            if (lane == 0) sm.nb_count = carry;
+        }
+        __syncthreads();
+        const int total = sm.nb_count;
         if (total <= cap) {
             uint32_t* L = links_n + soff;
-            for (int q = q0; q < q1; ++q) off += links_at(q, L, off);
+            int qx = col0, qy = row0;
+            for (int q = threadIdx.x; q - lane < N; q += kBlock, next_node(qx, qy)) {
+                const uint32_t bits = q < N ? ot[q] : 0u;
+                if (__ballot(bits != 0u) == 0ull) continue;
+                uint32_t before = (uint32_t)gtot[q >> 6];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const uint64_t m = __ballot((bits >> i & 1u) != 0u);
+                    before = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                                       __builtin_amdgcn_mbcnt_lo((uint32_t)m, before));
+                }
+                int gx, gy;
+                at_xy(qx, qy, gx, gy);
+                const uint32_t node = ((uint32_t)gy * (uint32_t)a.nx + (uint32_t)gx) << 4;
+                for (uint32_t m = bits; m != 0u; m &= m - 1u) L[before++] = node | (uint32_t)(__builtin_ctz(m) + 1);
+            }
         }
         if (threadIdx.x == 0) {
             seg_cnt_n[s] = total <= cap ? total : 0;

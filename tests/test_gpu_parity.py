@@ -553,3 +553,18 @@ def test_nan_warm_field_latches_enumeric(lbm_mod):
     with pytest.raises(lbm_mod.lbm.LBMError) as e:
         lat.check()
     assert e.value.status == lbm_mod.lbm.LBM_ENUMERIC
+
+
+@pytest.mark.parametrize("nx,ny,walls,body", [
+    (16, 15, True, lc.disc(7.3, 7.1, 1.0, vx=0.11, moves=True)),         # the box is wider than the lattice
+    (48, 47, False, lc.disc(20.2, 23.4, 17.9, vx=0.07, vy=-0.06, moves=True)),  # wraps on both axes
+    (160, 90, True, lc.disc(60.6, 44.2, 31.7, vx=-0.05, moves=True)),    # more than 64 nodes per box row
+    (120, 70, True, lc.box(50.5, 34.0, 0.0, 24.0, vx=0.06, moves=True))])  # one column of solid nodes
+def test_mover_boxes_f64(oracle_mod, lbm_mod, nx, ny, walls, body):
+    """Geometry, link lists and refill of a translating body by its swept
+    box: FP64 fields and forces against the oracle where the box is wider than
+    the lattice, wraps around it, or has rows longer than a wavefront."""
+    c = lc.make_case(nx, ny, 0.8, walls_y=walls, u0=(0.01, 0.0), bodies=[body], name="mover_boxes")
+    lat, osim = run_pair(oracle_mod, lbm_mod, c, 70)
+    compare_fields(lat, osim, 1e-12)
+    compare_forces(lat, osim, c, 1e-10)
