@@ -104,6 +104,7 @@ const char* batch_layout(const lbm_grid* grids, const double* taus, const lbm_so
         d.sa.walls = g.walls_y;
         d.sa.rho0 = g.rho0;
         d.cp64 = CollideParams<double>{g.rho0, 1.0 / taus[c], g.gx, g.gy, 1.0 - 1.0 / (2.0 * taus[c])};
+        fill_products(d.cp64);
         d.cp32 = CollideParams<float>{(float)g.rho0, (float)(1.0 / taus[c]), (float)g.gx, (float)g.gy,
                                       (float)(1.0 - 1.0 / (2.0 * taus[c]))};
         d.fa.nx = g.nx;
@@ -324,6 +325,7 @@ void batch_init_case(lbm_batch* b, int c, hipStream_t st, const void* rho, const
     cp.gx = (C)d.cp64.gx;
     cp.gy = (C)d.cp64.gy;
     cp.pref = (C)d.cp64.pref;
+    fill_products(cp);
     T* f = bws<T>(b, b->o_f) + d.f_off[b->t & 1];
     const uint8_t* own = bws<uint8_t>(b, b->o_own) + d.own_off;
     const lbm_grid& g = b->grids[c];
@@ -349,6 +351,7 @@ void batch_poiseuille_case(lbm_batch* b, int c, hipStream_t st) {
     cp.gx = (C)d.cp64.gx;
     cp.gy = (C)d.cp64.gy;
     cp.pref = (C)d.cp64.pref;
+    fill_products(cp);
     k_init_poiseuille<T><<<(unsigned)nb, kBlock, 0, st>>>(bws<T>(b, b->o_f) + d.f_off[b->t & 1],
                                                          bws<uint8_t>(b, b->o_own) + d.own_off, d.sa, cp,
                                                          b->grids[c].gx, b->taus[c]);

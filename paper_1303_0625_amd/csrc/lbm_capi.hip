@@ -41,7 +41,8 @@ size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 // Working sets above this use nontemporal loads/stores in the update kernel
 // (MI355X has a 256 MB Infinity Cache).
 constexpr size_t kStreamBytes = 256ull << 20;
-// Steps per captured graph of lbm_step (even: a block keeps its parity).
+// Steps per captured graph of lbm_step (a multiple of 4: a block of single or
+// of double steps is an even number of launches and keeps its buffer).
 constexpr int kGraphSteps = 32;
 
 size_t dtype_size(int dt) {
@@ -247,6 +248,10 @@ struct lbm_ctx {
     size_t ws_bytes;
     Layout L;
     int64_t t;
+    // population buffer and step-counter slot of the current state: every launch
+    // reads one and writes the other.  With translating bodies each launch takes
+    // one step and cur is the parity of t
+    int cur = 0;
     std::vector<int> movers_h, frees_h;  // prescribed and free translating bodies
     std::vector<char> is_free;           // by solid id
     double Gx = 0.0, Gy = 0.0;           // gravity on free bodies
@@ -258,8 +263,8 @@ struct lbm_ctx {
     std::vector<int> seg_off, seg_cap;
     int64_t link_cap_total;
     char err[512];
-    // blocks of kGraphSteps steps replayed as HIP graphs, one per start
-    // parity (every kernel argument is fixed by the parity; the step counter
+    // blocks of kGraphSteps steps replayed as HIP graphs, one per value of cur
+    // (every kernel argument is fixed by it; the step counter
     // lives on the device), captured on a stream of the context's own
     hipStream_t cap_stream = nullptr;
     hipGraphExec_t gexec[2] = {nullptr, nullptr};
@@ -312,6 +317,7 @@ CollideParams<C> collide_params(const lbm_ctx* c) {
     p.s_e = (C)c->mrt_s[0];
     p.s_eps = (C)c->mrt_s[1];
     p.s_q = (C)c->mrt_s[2];
+    fill_products(p);
     return p;
 }
 
@@ -364,22 +370,46 @@ uint8_t* own_ptr(lbm_ctx* c, int k) {
     return wsp<uint8_t>(c, c->L.own[k]);
 }
 
-// Enqueue one time step at parity p = t & 1 for storage type T: a single
-// launch whose workgroups compute the forces on G_t, move the translating
-// bodies (G_{t+1}, links, refill) and run the fused update.
+// Geometry that stays: no body translates (the second owner map then holds
+// the node flags, the second link buffer two more steps' force partials, and
+// both parities' link counts, velocities and rotations are alike).
+bool fixed_geometry(const lbm_ctx* c) { return c->L.n_movers == 0; }
+
+// Index of the current owner map, link list and link counts.
+int geo(const lbm_ctx* c) { return fixed_geometry(c) ? 0 : c->cur; }
+
+// Two steps per launch: fixed geometry, half-way bounce-back, BGK, FP64 or FP32
+// storage (profiling times single steps), and populations of at least 64 MiB.
+// (MRT: the compiler's own contraction of collide_mrt differs between the two
+// kernels in the last bit of FP64.)
+// Below that a launch has too few workgroups for its rows in series: per step,
+// two per launch against one, FP32 1024 x 1024 (36 MiB) 15.0 / 14.3 us, 2048 x
+// 1024 (72 MiB) 23.1 / 25.6 us, FP64 1001 x 517 (38 MiB) 15.1 / 14.4 us, 1024 x
+// 1024 (72 MiB) 20.1 / 23.9 us, 4096 x 2048 (576 MiB) 133 / 202 us.
+constexpr size_t kPairBytes = 64ull << 20;
+bool pairs(const lbm_ctx* c) {
+    return fixed_geometry(c) && !c->ibb && !c->mrt && !c->prof && (c->g.dtype == LBM_F64 || c->g.dtype == LBM_F32) &&
+           c->L.pbytes >= kPairBytes;
+}
+
+// Steps whose force totals a launch (or a reader) forms: the launch before may
+// have taken two.
+int pending_steps(const lbm_ctx* c) {
+    return fixed_geometry(c) && (c->g.dtype == LBM_F64 || c->g.dtype == LBM_F32) ? 2 : 1;
+}
+
 template <typename T>
-lbm_status enqueue_step(lbm_ctx* c) {
-    using C = typename Sto<T>::C;
-    const int p = (int)(c->t & 1);
+StepPtrs<T> step_ptrs(lbm_ctx* c) {
+    const int p = c->cur, q = geo(c);
     StepPtrs<T> sp;
     sp.fin = wsp<T>(c, c->L.f[p]);
     sp.fout = wsp<T>(c, c->L.f[p ^ 1]);
     sp.own_t = own_ptr(c, p);
     sp.own_n = own_ptr(c, p ^ 1);
-    sp.links_t = wsp<uint32_t>(c, c->L.links[p]);
-    sp.seg_cnt_t = wsp<int>(c, c->L.seg_cnt[p]);
-    sp.links_n = wsp<uint32_t>(c, c->L.links[p ^ 1]);
-    sp.seg_cnt_n = wsp<int>(c, c->L.seg_cnt[p ^ 1]);
+    sp.links_t = wsp<uint32_t>(c, c->L.links[q]);
+    sp.seg_cnt_t = wsp<int>(c, c->L.seg_cnt[q]);
+    sp.links_n = wsp<uint32_t>(c, c->L.links[q ^ 1]);
+    sp.seg_cnt_n = wsp<int>(c, c->L.seg_cnt[q ^ 1]);
     sp.seg_off = wsp<int>(c, c->L.seg_off);
     sp.seg_cap = wsp<int>(c, c->L.seg_cap);
     sp.chunk_solid = wsp<int>(c, c->L.chunk_solid);
@@ -391,14 +421,73 @@ lbm_status enqueue_step(lbm_ctx* c) {
     sp.rtab = wsp<double>(c, c->L.rtab) + (size_t)p * kRot * ns;
     sp.movers = wsp<int>(c, c->L.movers);
     sp.partial = wsp<double>(c, c->L.partial);
+    // (a chunk's 96 bytes fit its share of the link capacity: a body's is at
+    // least 288 links, the walls' 6 nx, and an empty list still has 256 bytes)
+    sp.partial_b = fixed_geometry(c) ? wsp<double>(c, c->L.links[1]) : sp.partial;
     sp.hist = wsp<double>(c, c->L.hist);
     sp.tctr = wsp<int64_t>(c, c->L.tctr);
     sp.errflag = wsp<int>(c, c->L.err);
+    return sp;
+}
+
+// Split of the two-step update: strips of equal width, at most kPairOut columns;
+// runs of about kPairRows rows, at least 4 (two waves of two).  Longer runs repeat
+// less work but keep more rows in flight at once, which costs more: 50 steps of
+// 4096 x 4096 FP32 with runs of 16 / 20 / 28 / 40 / 64 rows take 7.66 / 7.63 / 7.73 /
+// 8.18 / 9.15 ms.
+constexpr int kPairRows = 20;
+PairArgs pair_args(int nx, int ny) {
+    PairArgs a;
+    a.strips = (nx + kPairOut - 1) / kPairOut;
+    a.width = (nx + a.strips - 1) / a.strips;
+    a.strips = (nx + a.width - 1) / a.width;
+    a.runs = std::max(1, std::min((ny + kPairRows - 1) / kPairRows, ny / 4));
+    return a;
+}
+
+// Enqueue two time steps (pairs()): one launch.
+template <typename T>
+lbm_status enqueue_pair(lbm_ctx* c) {
+    using C = typename Sto<T>::C;
+    const StepPtrs<T> sp = step_ptrs<T>(c);
+    const PairArgs pa = pair_args(c->g.nx, c->g.ny);
+    RoleCounts rc;
+    rc.n_force = c->L.nchunks;
+    rc.n_move = 0;
+    rc.n_fin = 2;
+    rc.n_lead = (2 * rc.n_force + 1 + 7) / 8 * 8;
+    k_pair<T><<<(unsigned)(rc.n_lead + pa.strips * ((pa.runs + 7) / 8 * 8)), kBlock, 0, c->stream>>>(
+        sp, wsp<uint8_t>(c, c->L.own[1]), c->cur, rc, step_args(c), force_args(c), pa, collide_params<C>(c));
+    c->t += 2;
+    c->cur ^= 1;
+    return LBM_OK;
+}
+
+lbm_status dispatch_pair(lbm_ctx* c) {
+    return c->g.dtype == LBM_F64 ? enqueue_pair<double>(c) : enqueue_pair<float>(c);
+}
+
+// Node flags of a fixed geometry, from its owner map.
+void enqueue_flags(lbm_ctx* c) {
+    if (!fixed_geometry(c)) return;
+    k_node_flags<<<(unsigned)node_blocks(c), kBlock, 0, c->stream>>>(own_ptr(c, 0), wsp<uint8_t>(c, c->L.own[1]),
+                                                                     step_args(c));
+}
+
+// Enqueue one time step for storage type T: a single
+// launch whose workgroups compute the forces on G_t, move the translating
+// bodies (G_{t+1}, links, refill) and run the fused update.
+template <typename T>
+lbm_status enqueue_step(lbm_ctx* c) {
+    using C = typename Sto<T>::C;
+    const int p = c->cur, ns = c->n + 1;
+    const StepPtrs<T> sp = step_ptrs<T>(c);
     const int n_presc = (int)c->movers_h.size(), n_free = (int)c->frees_h.size();
     RoleCounts rc;
     rc.n_force = c->L.nchunks;
     rc.n_move = 2 * n_presc;  // geometry and refill workgroup per prescribed mover
     rc.n_bnd = c->ibb ? 2 * c->L.nchunks : 0;  // boundary role: two per link chunk
+    rc.n_fin = pending_steps(c);
     rc.n_lead = (rc.n_force + rc.n_move + 1 + rc.n_bnd + 7) / 8 * 8;
     MoveArgs ma{c->g.nx, c->g.ny, c->L.opitch, c->g.walls_y, (int64_t)c->L.pitch,
                 9 * (int64_t)c->L.pitch, c->g.rho0, c->g.refill, c->L.box_bytes, n_presc};
@@ -452,6 +541,7 @@ lbm_status enqueue_step(lbm_ctx* c) {
         kf<<<2 * n_free, kBlock, 2 * (size_t)c->L.box_bytes, c->stream>>>(fp, p, fm, fr, cp);
     }
     c->t += 1;
+    c->cur ^= 1;
     return LBM_OK;
 }
 
@@ -467,7 +557,7 @@ lbm_status dispatch_step(lbm_ctx* c) {
 template <typename T, typename FT>
 void enqueue_init(lbm_ctx* c, const FT* rho, const FT* ux, const FT* uy) {
     using C = typename Sto<T>::C;
-    const int p = (int)(c->t & 1);
+    const int p = c->cur;
     k_init<T, FT><<<(unsigned)node_blocks(c), kBlock, 0, c->stream>>>(
         wsp<T>(c, c->L.f[p]), own_ptr(c, p), step_args(c), collide_params<C>(c), c->g.u0x,
         c->g.u0y, rho, ux, uy);
@@ -476,7 +566,7 @@ void enqueue_init(lbm_ctx* c, const FT* rho, const FT* ux, const FT* uy) {
 template <typename T>
 void enqueue_init_poiseuille(lbm_ctx* c) {
     using C = typename Sto<T>::C;
-    const int p = (int)(c->t & 1);
+    const int p = c->cur;
     k_init_poiseuille<T><<<(unsigned)node_blocks(c), kBlock, 0, c->stream>>>(
         wsp<T>(c, c->L.f[p]), own_ptr(c, p), step_args(c), collide_params<C>(c), c->g.gx, c->tau);
 }
@@ -565,21 +655,22 @@ void drop_graphs(lbm_ctx* c) {
         }
 }
 
-// Capture kGraphSteps steps starting at parity p into c->gexec[p].
+// Capture kGraphSteps steps starting at buffer p = cur into c->gexec[p].
 lbm_status capture_block(lbm_ctx* c, int p) {
     if (!c->cap_stream) HIPCHK(c, hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking));
     hipStream_t user = c->stream;
-    const int64_t tsave = c->t;
-    c->t = p;  // only the parity of t enters the launches
+    const int64_t tsave = c->t;  // (t itself does not enter the launches)
     c->stream = c->cap_stream;
     hipError_t e = hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeThreadLocal);
     lbm_status rs = LBM_OK;
     if (e == hipSuccess)
-        for (int k = 0; k < kGraphSteps && rs == LBM_OK; ++k) rs = dispatch_step(c);
+        for (int k = 0; k < kGraphSteps && rs == LBM_OK; k += pairs(c) ? 2 : 1)
+            rs = pairs(c) ? dispatch_pair(c) : dispatch_step(c);
     hipGraph_t g = nullptr;
     hipError_t e2 = e == hipSuccess ? hipStreamEndCapture(c->cap_stream, &g) : e;
     c->stream = user;
     c->t = tsave;
+    c->cur = p;  // (an even number of launches)
     if (e != hipSuccess) return hip_fail(c, e, "hipStreamBeginCapture");
     if (e2 != hipSuccess) return hip_fail(c, e2, "hipStreamEndCapture");
     if (rs != LBM_OK) {
@@ -598,9 +689,7 @@ lbm_status capture_block(lbm_ctx* c, int p) {
 // Sum the last step's force totals if a reader needs them.
 void finalize_pending(lbm_ctx* c) {
     if (!c->fin_pending) return;
-    k_finalize<<<1, kBlock, 0, c->stream>>>(wsp<double>(c, c->L.partial), wsp<int>(c, c->L.solid_chunk0),
-                                            wsp<double>(c, c->L.hist), wsp<int64_t>(c, c->L.tctr),
-                                            (int)(c->t & 1), force_args(c));
+    k_finalize<float><<<1, kBlock, 0, c->stream>>>(step_ptrs<float>(c), c->cur, pending_steps(c), force_args(c));
     c->fin_pending = false;
 }
 
@@ -780,6 +869,7 @@ lbm_status lbm_create(const lbm_grid* grid, double tau, const lbm_solid* solids,
     if (e == hipSuccess)
         e = hipMemcpyAsync(c->ws + L.seg_cnt[1], c->ws + L.seg_cnt[0], 4 * (size_t)ns,
                            hipMemcpyDeviceToDevice, st);
+    enqueue_flags(c);
     dispatch_init<double>(c, nullptr, nullptr, nullptr);
     if (e == hipSuccess) e = hipGetLastError();
     if (e == hipSuccess) e = hipStreamSynchronize(st);
@@ -861,7 +951,7 @@ lbm_status lbm_step(lbm_ctx* c, int64_t n) {
     // whole blocks as graph replays (not while timing single launches, and
     // not for a context that must not allocate: instantiating a graph may)
     while (!c->prof && c->static_dev < 0 && n - k >= kGraphSteps) {
-        const int p = (int)(c->t & 1);
+        const int p = c->cur;
         if (!c->gexec[p]) {
             lbm_status rs = capture_block(c, p);
             if (rs != LBM_OK) return rs;
@@ -870,9 +960,11 @@ lbm_status lbm_step(lbm_ctx* c, int64_t n) {
         c->t += kGraphSteps;
         k += kGraphSteps;
     }
-    for (; k < n; ++k) {
-        lbm_status s = dispatch_step(c);
+    while (k < n) {
+        const bool two = pairs(c) && n - k >= 2;
+        lbm_status s = two ? dispatch_pair(c) : dispatch_step(c);
         if (s != LBM_OK) return s;
+        k += two ? 2 : 1;
     }
     c->fin_pending = true;
     HIPCHK(c, hipGetLastError());
@@ -937,7 +1029,7 @@ lbm_status lbm_fields(lbm_ctx* c, void* d_rho, void* d_ux, void* d_uy, int32_t o
         set_err(c->err, "fields are written as LBM_F64 or LBM_F32");
         return LBM_EINVAL;
     }
-    const int p = (int)(c->t & 1);
+    const int p = c->cur;
     StepArgs sa = step_args(c);
     const uint8_t* own = own_ptr(c, p);
     int* errf = wsp<int>(c, c->L.err);
@@ -1128,7 +1220,7 @@ lbm_status lbm_init_poiseuille(lbm_ctx* c) {
 
 lbm_status lbm_populations(lbm_ctx* c, double* d_out) {
     if (!c || !d_out) return LBM_EINVAL;
-    const int p = (int)(c->t & 1);
+    const int p = c->cur;
     StepArgs sa = step_args(c);
     const unsigned nb = (unsigned)node_blocks(c);
     const uint8_t* own = own_ptr(c, p);
@@ -1146,8 +1238,7 @@ lbm_status lbm_link_forces(lbm_ctx* c, double* d_out, int64_t max, int64_t* n) {
     if (!c || !n) return LBM_EINVAL;
     const int ns = c->n + 1;
     std::vector<int> cnt(ns), roff(ns);
-    const int pc = (int)(c->t & 1);
-    HIPCHK(c, hipMemcpyAsync(cnt.data(), wsp<int>(c, c->L.seg_cnt[pc]), sizeof(int) * ns,
+    HIPCHK(c, hipMemcpyAsync(cnt.data(), wsp<int>(c, c->L.seg_cnt[geo(c)]), sizeof(int) * ns,
                              hipMemcpyDeviceToHost, c->stream));
     lbm_status rs = read_err(c);
     if (rs != LBM_OK) return rs;
@@ -1164,10 +1255,10 @@ lbm_status lbm_link_forces(lbm_ctx* c, double* d_out, int64_t max, int64_t* n) {
     if (tot == 0) return LBM_OK;
     HIPCHK(c, hipMemcpyAsync(wsp<int>(c, c->L.rec_off), roff.data(), sizeof(int) * ns,
                              hipMemcpyHostToDevice, c->stream));
-    const int p = (int)(c->t & 1);
+    const int p = c->cur;
     ForceArgs fa = force_args(c);
-    const uint32_t* links = wsp<uint32_t>(c, c->L.links[p]);
-    const int* sc = wsp<int>(c, c->L.seg_cnt[p]);
+    const uint32_t* links = wsp<uint32_t>(c, c->L.links[geo(c)]);
+    const int* sc = wsp<int>(c, c->L.seg_cnt[geo(c)]);
     const int* so = wsp<int>(c, c->L.seg_off);
     const int* ro = wsp<int>(c, c->L.rec_off);
     const SolidDev* sol = wsp<SolidDev>(c, c->L.sol);
@@ -1212,7 +1303,7 @@ lbm_status lbm_save(lbm_ctx* c, void* d_dst, size_t bytes) {
     }
     char* d = (char*)d_dst;
     int64_t hdr[8] = {0x6c626d63, (int64_t)LBM_ABI_VERSION, c->t, c->g.nx, c->g.ny, c->g.dtype, c->n, 0};
-    const int p = (int)(c->t & 1);
+    const int p = c->cur;
     const size_t fb = c->L.pbytes, sb = c->L.sbytes, rb = c->L.rbytes;
     const size_t ob = c->L.own[1] - c->L.own[0];
     HIPCHK(c, hipMemcpyAsync(d, hdr, 64, hipMemcpyHostToDevice, c->stream));
@@ -1228,9 +1319,9 @@ lbm_status lbm_save(lbm_ctx* c, void* d_dst, size_t bytes) {
     HIPCHK(c, hipMemcpyAsync(d + o, own_ptr(c, p ^ 1), ob, hipMemcpyDeviceToDevice, c->stream));
     o += ob;
     const size_t lb = 4 * (size_t)std::max<int64_t>(c->link_cap_total, 1);
-    HIPCHK(c, hipMemcpyAsync(d + o, c->ws + c->L.links[p], lb, hipMemcpyDeviceToDevice, c->stream));
+    HIPCHK(c, hipMemcpyAsync(d + o, c->ws + c->L.links[geo(c)], lb, hipMemcpyDeviceToDevice, c->stream));
     o += lb;
-    HIPCHK(c, hipMemcpyAsync(d + o, c->ws + c->L.seg_cnt[p], 4 * (size_t)(c->n + 1), hipMemcpyDeviceToDevice, c->stream));
+    HIPCHK(c, hipMemcpyAsync(d + o, c->ws + c->L.seg_cnt[geo(c)], 4 * (size_t)(c->n + 1), hipMemcpyDeviceToDevice, c->stream));
     return read_err(c);
 }
 
@@ -1256,7 +1347,8 @@ lbm_status lbm_load(lbm_ctx* c, const void* d_src, size_t bytes) {
         return LBM_EINVAL;
     }
     c->t = hdr[2];
-    const int p = (int)(c->t & 1);
+    c->cur = (int)(c->t & 1);
+    const int p = c->cur;
     const size_t fb = c->L.pbytes, sb = c->L.sbytes, rb = c->L.rbytes;
     const size_t ob = c->L.own[1] - c->L.own[0];
     size_t o = 64;
@@ -1272,9 +1364,10 @@ lbm_status lbm_load(lbm_ctx* c, const void* d_src, size_t bytes) {
         HIPCHK(c, hipMemcpyAsync(own_ptr(c, p ^ 1), s + o, ob, hipMemcpyDeviceToDevice, c->stream));
     o += ob;
     const size_t lb = 4 * (size_t)std::max<int64_t>(c->link_cap_total, 1);
-    HIPCHK(c, hipMemcpyAsync(c->ws + c->L.links[p], s + o, lb, hipMemcpyDeviceToDevice, c->stream));
+    HIPCHK(c, hipMemcpyAsync(c->ws + c->L.links[geo(c)], s + o, lb, hipMemcpyDeviceToDevice, c->stream));
     o += lb;
-    HIPCHK(c, hipMemcpyAsync(c->ws + c->L.seg_cnt[p], s + o, 4 * (size_t)(c->n + 1), hipMemcpyDeviceToDevice, c->stream));
+    HIPCHK(c, hipMemcpyAsync(c->ws + c->L.seg_cnt[geo(c)], s + o, 4 * (size_t)(c->n + 1), hipMemcpyDeviceToDevice, c->stream));
+    enqueue_flags(c);
     k_set_counters<<<1, 1, 0, c->stream>>>(wsp<int64_t>(c, c->L.tctr), c->t, wsp<int>(c, c->L.err));
     c->hist_first = c->t;  // force records before the checkpoint are not restored
     c->fin_pending = false;

@@ -121,7 +121,25 @@ struct CollideParams {
     C rho0, omega, gx, gy, pref;  // pref = 1 - 1/(2 tau)
     int mrt;                      // 1: multiple-relaxation-time operator (below)
     C s_e, s_eps, s_q;            // its energy, energy-square and heat-flux rates
+    // products of the above that collide<double> takes as scalars (fill_products):
+    // 1 - omega, g / 2, 3 pref, and 9 w pref, 3 w pref, 3 w, 4.5 w of the axis
+    // [0] and diagonal [1] directions
+    C keep, hgx, hgy, p3, p9[2], p3w[2], w3[2], w45[2];
 };
+inline void fill_products(CollideParams<double>& p) {
+    p.keep = 1.0 - p.omega;
+    p.hgx = 0.5 * p.gx;
+    p.hgy = 0.5 * p.gy;
+    p.p3 = 3.0 * p.pref;
+    for (int k = 0; k < 2; ++k) {
+        const double w = w_<double>(k == 0 ? 1 : 5);
+        p.p9[k] = (9.0 * w) * p.pref;
+        p.p3w[k] = (3.0 * w) * p.pref;
+        p.w3[k] = 3.0 * w;
+        p.w45[k] = 4.5 * w;
+    }
+}
+inline void fill_products(CollideParams<float>&) {}
 
 // 1/x: a correctly rounded division in FP64; in FP32, the arithmetic of the
 // 16-bit storages, the hardware reciprocal (within 1 ulp, far below the
@@ -201,6 +219,50 @@ __device__ inline void collide(C d[9], const CollideParams<C>& p, Moments<C>* mo
     pair(2, 4, m.uy, Fy, w_<C>(2));
     pair(5, 7, m.ux + m.uy, Fx + Fy, w_<C>(5));
     pair(6, 8, m.uy - m.ux, Fy - Fx, w_<C>(6));
+}
+
+// The same in FP64 with the fused multiply-adds written out and no other
+// contraction: which of two products the compiler fuses depends on their uses
+// around the call, and every kernel that collides a node (one step or two per
+// launch, single lattices or batches) has to give the same bits.
+template <>
+__device__ inline Moments<double> moments<double>(const double d[9], const CollideParams<double>& p) {
+#pragma clang fp contract(off)
+    Moments<double> m;
+    m.drho = ((d[0] + d[1]) + (d[2] + d[3])) + ((d[4] + d[5]) + (d[6] + d[7])) + d[8];
+    m.rho = p.rho0 + m.drho;
+    const double jx = (d[1] - d[3]) + (d[5] - d[6]) + (d[8] - d[7]);
+    const double jy = (d[2] - d[4]) + (d[5] + d[6]) - (d[7] + d[8]);
+    const double inv = recip<double>(m.rho);
+    m.ux = jx * inv + p.hgx;
+    m.uy = jy * inv + p.hgy;
+    return m;
+}
+template <>
+__device__ inline void collide<double>(double d[9], const CollideParams<double>& p, Moments<double>* mo_out,
+                                       const Moments<double>* mo_in) {
+#pragma clang fp contract(off)
+    const Moments<double> m = mo_in ? *mo_in : moments<double>(d, p);
+    if (mo_out) *mo_out = m;
+    const double om = p.omega, keep = p.keep;
+    const double Fx = m.rho * p.gx, Fy = m.rho * p.gy;
+    const double uu = __builtin_fma(m.ux, m.ux, m.uy * m.uy);
+    const double uF = __builtin_fma(m.ux, Fx, m.uy * Fy);
+    const double z = __builtin_fma(om, __builtin_fma(-(1.5 * m.rho), uu, m.drho), -(p.p3 * uF));
+    const double orho = om * m.rho;
+    d[0] = __builtin_fma(keep, d[0], w_<double>(0) * z);
+    auto pair = [&](int i, int j, double eu, double eF, int k) {
+#pragma clang fp contract(off)
+        const double t = __builtin_fma(p.p9[k], eF, (p.w45[k] * orho) * eu);
+        const double A = __builtin_fma(eu, t, w_<double>(i) * z);
+        const double B = __builtin_fma(p.p3w[k], eF, (p.w3[k] * orho) * eu);
+        d[i] = __builtin_fma(keep, d[i], A + B);
+        d[j] = __builtin_fma(keep, d[j], A - B);
+    };
+    pair(1, 3, m.ux, Fx, 0);
+    pair(2, 4, m.uy, Fy, 0);
+    pair(5, 7, m.ux + m.uy, __builtin_fma(p.gy, m.rho, Fx), 1);
+    pair(6, 8, m.uy - m.ux, __builtin_fma(p.gy, m.rho, -Fx), 1);
 }
 
 // Multiple-relaxation-time collision (Sec. IV) on the deviations, over the

@@ -1450,10 +1450,11 @@ struct LinkEval {
     double av, bv, vx, vy, rx, ry;
 };
 
+// known: the population f~_i(x_f) - w_i rho0 when the caller has formed it.
 template <typename T, bool GEO>
 __device__ inline LinkEval eval_link(const T* __restrict__ f, const uint8_t* __restrict__ own_t,
                                      const SolidDev& S, double X, double Y, double vbx, double vby, double om,
-                                     int s, int x, int y, int i, const ForceArgs& a) {
+                                     int s, int x, int y, int i, const ForceArgs& a, const double* known = nullptr) {
     const double ex = ex_(i), ey = ey_(i), w = w_<double>(i);
     double q = 0.5;
     if constexpr (GEO)
@@ -1468,7 +1469,7 @@ __device__ inline LinkEval eval_link(const T* __restrict__ f, const uint8_t* __r
     }
     L.vx = vbx - om * L.ry;
     L.vy = vby + om * L.rx;
-    L.av = w * a.rho0 + (double)pop_at(f, a, i, x, y);
+    L.av = w * a.rho0 + (known ? *known : (double)pop_at(f, a, i, x, y));
     const double m = 6.0 * w * a.rho0 * (ex * L.vx + ey * L.vy);
     L.bv = L.av - m;
     if constexpr (!GEO) return L;
@@ -1514,8 +1515,11 @@ struct ForceShared {
     double red[kBlock / 64][6];
 };
 
-// GEO: interpolated bounce-back may be on (a.ibb).
-template <typename T, bool GEO>
+// GEO: interpolated bounce-back may be on (a.ibb).  next(x, y, i): when given,
+// the population f~_i(x_f) - w_i rho0 to take instead of the stored one (the
+// links of the step after the stored state).
+struct StoredPop {};
+template <typename T, bool GEO, typename Next = StoredPop>
 __device__ inline void force_role(int c, ForceShared& fs, const T* __restrict__ f,
                                   const uint8_t* __restrict__ own_t, const uint32_t* __restrict__ links,
                                   const int* __restrict__ seg_cnt, const int* __restrict__ seg_off,
@@ -1523,7 +1527,7 @@ __device__ inline void force_role(int c, ForceShared& fs, const T* __restrict__ 
                                   const int* __restrict__ chunk_start,
                                   const SolidDev* __restrict__ sol, const double* __restrict__ vt,
                                   const double* __restrict__ rt, double* __restrict__ partial,
-                                  int64_t t, const ForceArgs& a) {
+                                  int64_t t, const ForceArgs& a, const Next& next = Next()) {
     const int s = chunk_solid[c];
     const int start = chunk_start[c];
     const int n = seg_cnt[s];
@@ -1549,7 +1553,11 @@ __device__ inline void force_role(int c, ForceShared& fs, const T* __restrict__ 
         const int y = (int)(node / (uint32_t)a.nx);
         const int x = (int)(node - (uint32_t)y * (uint32_t)a.nx);
         const double ex = ex_(i), ey = ey_(i);
-        const LinkEval le = eval_link<T, GEO>(f, own_t, S, X, Y, vbx, vby, om, s, x, y, i, a);
+        double pop = 0.0;
+        constexpr bool kStored = __is_same(Next, StoredPop);
+        if constexpr (!kStored) pop = next(x, y, i);
+        const LinkEval le =
+            eval_link<T, GEO>(f, own_t, S, X, Y, vbx, vby, om, s, x, y, i, a, kStored ? nullptr : &pop);
         const double av = le.av, bv = le.bv, vx = le.vx, vy = le.vy, rx = le.rx, ry = le.ry;
         // CME: e_i a - e_ibar b, e_ibar = -e_i
         const double cfx = ex * av + ex * bv;
@@ -1593,18 +1601,6 @@ __device__ inline void finalize_forces(const double* __restrict__ partial,
     }
 }
 
-// Finalize the forces of step tctr[parity] - 1 (after the last launch of a
-// batch of steps); partials of step u live in partial[(u & 1)].
-__global__ __launch_bounds__(kBlock) void k_finalize(const double* __restrict__ partial2,
-                                                     const int* __restrict__ solid_chunk0,
-                                                     double* __restrict__ hist,
-                                                     const int64_t* __restrict__ tctr, int parity,
-                                                     ForceArgs a) {
-    const int64_t t = tctr[parity];
-    if (t < 1) return;
-    finalize_forces(partial2 + (size_t)((t - 1) & 1) * a.nchunks * 6, solid_chunk0, hist, t - 1, a);
-}
-
 // ------------------------------------------------------------------ fused step
 // One launch per time step: workgroups [0, n_force) are force chunks,
 // [n_force, n_force + n_move) are translating bodies, workgroup
@@ -1632,15 +1628,37 @@ struct StepPtrs {
     const double* vtab;
     const double* rtab;  // rotation table of this step
     const int* movers;
-    double* partial;  // [2][nchunks][6], by step parity
+    double* partial;    // [2][nchunks][6]: steps u with (u & 2) == 0, by parity
+    double* partial_b;  // the same for (u & 2) != 0 (translating bodies: `partial` again)
     double* hist;
-    int64_t* tctr;
+    int64_t* tctr;      // step counter, slot toggled by every launch
     int* errflag;
+    __device__ inline double* part(int64_t u, int nchunks) const {
+        return ((u & 2) != 0 ? partial_b : partial) + (size_t)(u & 1) * nchunks * 6;
+    }
 };
+
+// Totals of the last `count` (1 or 2) steps before step t, oldest first (a
+// history of one step keeps the last).
+template <typename T>
+__device__ inline void finalize_last(const StepPtrs<T>& p, int64_t t, int count, const ForceArgs& a) {
+    for (int64_t u = t - count; u < t; ++u) {
+        if (u >= 0) finalize_forces(p.part(u, a.nchunks), p.solid_chunk0, p.hist, u, a);
+        __syncthreads();
+    }
+}
+
+// Finalize the forces of the last launch's steps (after the last launch of a
+// batch of steps).
+template <typename T>
+__global__ __launch_bounds__(kBlock) void k_finalize(StepPtrs<T> p, int slot, int count, ForceArgs a) {
+    finalize_last(p, p.tctr[slot], count, a);
+}
 
 struct RoleCounts {
     int n_force, n_move, n_lead;
     int n_bnd = 0;  // boundary workgroups (interpolated bounce-back, two per force chunk)
+    int n_fin = 1;  // steps whose totals are formed (2 when the launch before may have taken two)
 };
 
 // Boundary role (interpolated bounce-back): workgroup c takes the links of
@@ -1689,7 +1707,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(GEO ? 4 
         const int64_t t = p.tctr[parity];
         if (b < rc.n_force) {
             force_role<T, GEO>(b, sh.f, p.fin, p.own_t, p.links_t, p.seg_cnt_t, p.seg_off, p.chunk_solid, p.chunk_start,
-                          p.sol, p.vtab, p.rtab, p.partial + (size_t)(t & 1) * fa.nchunks * 6, t, fa);
+                          p.sol, p.vtab, p.rtab, p.part(t, fa.nchunks), t, fa);
         } else if (b < rc.n_force + rc.n_move) {
             move_role<T, MRT, GEO>(b - rc.n_force, dyn_lds, sh.m, p.fin, p.fout, p.own_t, p.own_n, p.links_n,
                          p.seg_cnt_n, p.seg_off, p.seg_cap, p.sol, p.vtab, p.rtab, p.movers, p.tctr, parity,
@@ -1697,9 +1715,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(GEO ? 4 
         } else if (b == rc.n_force + rc.n_move) {
             // previous step's totals (its partials are complete: the
             // previous launch has ended); then advance the step counter
-            if (t >= 1)
-                finalize_forces(p.partial + (size_t)((t - 1) & 1) * fa.nchunks * 6, p.solid_chunk0, p.hist,
-                                t - 1, fa);
+            finalize_last(p, t, rc.n_fin, fa);
             if (threadIdx.x == 0) p.tctr[parity ^ 1] = t + 1;
         } else if constexpr (GEO) {
             const int c = b - (rc.n_force + rc.n_move + 1);
@@ -1710,6 +1726,405 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(GEO ? 4 
     const int64_t t = GEO ? p.tctr[parity] : 0;
     step_role<T, NT, MRT, GEO>((uint32_t)(b - rc.n_lead), gridDim.x - (uint32_t)rc.n_lead, p.fin, p.fout,
                                p.own_t, p.vtab, p.rtab, p.sol, t, sa, cp);
+}
+
+// ------------------------------------------------------------------ two steps per launch
+// Large lattices whose geometry stays (no translating body, half-way bounce-back,
+// BGK, FP64 or FP32 storage) take two steps per pass over memory: the state between
+// them stays in registers.  A workgroup owns a strip of at most kPairOut columns
+// over a run of rows, each of its four waves marching along y over a quarter.  Per row r it pulls, bounces and
+// collides row r of the state at t + 1 from memory (all 64 lanes, the strip
+// and one column on each side; the next row's loads are in flight meanwhile),
+// and then row r - 1 of the state at t + 2 from registers: the populations that
+// stream along y are kept from the rows before, those that stream along x come
+// from the neighbouring lanes by a wavefront shift, so the rows need neither LDS
+// nor a barrier; the four waves meet once, at the end, to finish the rows where
+// their runs touch.  The state at
+// t + 1 is rounded to the storage type as if it had been stored: results equal
+// two single steps bit for bit.
+//
+// Bytes: a pass reads and writes each population once for two steps (4096 x 4096
+// FP32: 1.3 GB of traffic per launch).  Work done twice: the two columns beside a
+// strip and the two rows beside a workgroup's run.  Per step on 4096 x 4096: FP32
+// 203 us one step per launch, 150 us two per launch; FP64 4096 x 2048: 202, 133 us.
+// Bound by the loads in flight: without its arithmetic the launch takes 285 us
+// (4.5 TB/s), without memory traffic 206 us, together 295 us; its 111 registers
+// allow 16 waves per compute unit of one row's loads each, and a second row in
+// flight spills (372 us).  Measured around it (per launch): strips of 62 / 56 / 48
+// / 32 columns 310 / 295 / 304 / 398 us (56 FP32 columns are whole 32-byte
+// sectors; whole lines cost too many lanes); nontemporal loads 385 us (the lines
+// that neighbouring strips share are fetched twice), nontemporal stores 308 us.
+constexpr int kPairOut = 56;
+
+// Node flags of a lattice whose geometry stays.
+constexpr uint8_t kNodeBulk = 0, kNodeSolid = 1, kNodeNear = 2;  // near: a neighbour is solid or a wall row
+
+__global__ __launch_bounds__(kBlock) void k_node_flags(const uint8_t* __restrict__ own, uint8_t* __restrict__ flags,
+                                                       StepArgs a) {
+    const int64_t idx = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const int y = (int)(idx / a.rowlen);
+    const int x = (int)(idx - (int64_t)y * a.rowlen);
+    if (y >= a.ny || x >= a.nx) return;
+    const int64_t o = (int64_t)y * a.opitch + x;
+    flags[o] = own[o] != 0 ? kNodeSolid : (next_to_solid(own, a, x, y) ? kNodeNear : kNodeBulk);
+}
+
+// Value of lane - 1 (shift right) and of lane + 1 (shift left) of the wave; the
+// first and the last lane's are not used.
+__device__ inline float lane_before(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x138, 0xf, 0xf, true));
+}
+__device__ inline float lane_after(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x130, 0xf, 0xf, true));
+}
+template <int CTRL>
+__device__ inline double lane_shift64(double v) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, 0xf, 0xf, true);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, 0xf, 0xf, true);
+    return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+__device__ inline double lane_before(double v) { return lane_shift64<0x138>(v); }
+__device__ inline double lane_after(double v) { return lane_shift64<0x130>(v); }
+
+// Half-way bounce-back of a near node (x, y): every direction whose source is
+// solid or a wall row takes mine(opposite direction) plus the moving-wall term.
+template <typename C, typename Mine>
+__device__ inline void bounce_back(C d[9], int xm, int x, int xp, int y, const uint8_t* __restrict__ own,
+                                   const double* __restrict__ vtab, const StepArgs& a, const Mine& mine) {
+    int ym = y - 1, yp = y + 1;
+    bool wall_lo = false, wall_hi = false;
+    if (a.walls) {
+        wall_lo = y == 0;
+        wall_hi = y == a.ny - 1;
+    }
+    ym = ym < 0 ? (wall_lo ? y : a.ny - 1) : ym;
+    yp = yp >= a.ny ? (wall_hi ? y : 0) : yp;
+    const uint8_t* om = own + (int64_t)ym * a.opitch;
+    const uint8_t* o0 = own + (int64_t)y * a.opitch;
+    const uint8_t* op = own + (int64_t)yp * a.opitch;
+    const uint32_t src[9] = {0u, o0[xm], om[x], o0[xp], op[x], om[xm], om[xp], op[xp], op[xm]};
+#pragma unroll
+    for (int i = 1; i < 9; ++i) {
+        const bool wall = (ey_(i) == 1 && wall_lo) || (ey_(i) == -1 && wall_hi);
+        const uint32_t sid = wall ? 0u : src[i];
+        if (wall || sid != 0u) {
+            const C vx = (C)vtab[2 * sid], vy = (C)vtab[2 * sid + 1];
+            d[i] = mine(opp_(i)) + C(6) * w_<C>(i) * (C)a.rho0 * (C(ex_(i)) * vx + C(ey_(i)) * vy);
+        }
+    }
+}
+
+// Source columns of x, periodic.
+__device__ inline void side_columns(int x, int nx, int& xm, int& xp) {
+    xm = x == 0 ? nx - 1 : x - 1;
+    xp = x == nx - 1 ? 0 : x + 1;
+}
+
+// State at t + 1 of a near fluid node, rounded to the storage type (the links'
+// forces of step t + 1).
+template <typename T>
+__device__ inline double next_pop(const T* __restrict__ fin, const uint8_t* __restrict__ own,
+                                  const double* __restrict__ vtab, const StepArgs& a,
+                                  const CollideParams<typename Sto<T>::C>& cp, int x, int y, int i) {
+    using C = typename Sto<T>::C;
+    int xm, xp;
+    side_columns(x, a.nx, xm, xp);
+    // (where the source row is a wall the value is replaced: any row serves)
+    const int ym = y == 0 ? (a.walls ? 0 : a.ny - 1) : y - 1, yp = y == a.ny - 1 ? (a.walls ? y : 0) : y + 1;
+    const T* r0 = fin + (int64_t)y * a.ystride;
+    T raw[9], mine[9];
+#pragma unroll
+    for (int j = 0; j < 9; ++j) {
+        const T* row = fin + (int64_t)(ey_(j) == 1 ? ym : (ey_(j) == -1 ? yp : y)) * a.ystride + j * a.istride;
+        raw[j] = row[ex_(j) == 1 ? xm : (ex_(j) == -1 ? xp : x)];
+        mine[j] = r0[j * a.istride + x];
+    }
+    C d[9];
+#pragma unroll
+    for (int j = 0; j < 9; ++j) d[j] = Sto<T>::ld(raw[j]);
+    bounce_back<C>(d, xm, x, xp, y, own, vtab, a, [&](int j) -> C { return Sto<T>::ld(mine[j]); });
+    collide<C>(d, cp);
+    double v = 0.0;
+#pragma unroll
+    for (int j = 1; j < 9; ++j) v = j == i ? (double)Sto<T>::ld(Sto<T>::st(d[j])) : v;
+    return v;
+}
+
+// Loads and stores through a buffer descriptor of one lattice row: a scalar
+// base, a scalar row offset and a 32-bit lane offset (in a loop over rows the
+// compiler would fold scalar base and lane offset into one 64-bit vector address
+// per access).  A store past the row's end writes nothing: lanes without an
+// output take such an offset instead of a branch, so that the number of memory
+// operations in flight is known at every point of the loop (with a branch around
+// them, the wait for the next row's loads became a wait for the stores too).
+// (p is wave-uniform; reading it through the first lane keeps the descriptor in
+// scalar registers whichever unit formed the address)
+template <typename T>
+__device__ inline __amdgpu_buffer_rsrc_t buffer_of(const T* p, uint32_t bytes) {
+    const uint64_t u = reinterpret_cast<uint64_t>(p);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)u);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(u >> 32));
+    return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>((uint64_t)hi << 32 | lo), 0, (int)bytes,
+                                             0x00020000);
+}
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+__device__ inline void st_buffer(float v, __amdgpu_buffer_rsrc_t r, uint32_t at, uint32_t row) {
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r, (int)at, (int)row, 0);
+}
+__device__ inline void st_buffer(double v, __amdgpu_buffer_rsrc_t r, uint32_t at, uint32_t row) {
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, (int)at, (int)row, 0);
+}
+__device__ inline void ld_buffer(float& v, __amdgpu_buffer_rsrc_t r, uint32_t at, uint32_t row) {
+    v = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, (int)at, (int)row, 0));
+}
+__device__ inline void ld_buffer(double& v, __amdgpu_buffer_rsrc_t r, uint32_t at, uint32_t row) {
+    const u32x2 u = __builtin_amdgcn_raw_buffer_load_b64(r, (int)at, (int)row, 0);
+    v = __builtin_bit_cast(double, u);
+}
+
+// Values that neighbouring waves of a workgroup exchange, one per lane: what a
+// wave's last row sends up, what its first row sends down, and its first row's
+// own state and incoming populations, kept until the row below is known.
+template <typename T>
+struct PairShared {
+    T up[kBlock / 64][3][64], down[kBlock / 64][3][64], first[kBlock / 64][12][64];
+};
+
+// Columns [x0, x0 + nout) of rows [Ya, Yb) at t + 2: one workgroup, its waves on
+// consecutive runs of at least two rows.
+template <typename T>
+__device__ inline void pair_strip(PairShared<T>& sh, const T* __restrict__ fin, T* __restrict__ fout,
+                                  const uint8_t* __restrict__ own, const uint8_t* __restrict__ flags,
+                                  const double* __restrict__ vtab, int x0, int nout, int Ya, int Yb,
+                                  const StepArgs& a, const CollideParams<typename Sto<T>::C>& cp) {
+    using C = typename Sto<T>::C;
+    constexpr uint32_t ES = sizeof(T);
+    const int lane = (int)threadIdx.x & 63, wave = (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int rows = Yb - Ya, nw = rows / 2 < kBlock / 64 ? rows / 2 : kBlock / 64;
+    const int ya = Ya + rows * wave / nw, yb = Ya + rows * (wave + 1) / nw;
+    const bool lowest = wave == 0, highest = wave == nw - 1;
+    // the lane's column: one before the strip, the strip, one after it
+    int x = x0 - 1 + (lane <= nout ? lane : nout + 1);
+    x = x < 0 ? x + a.nx : (x >= a.nx ? x - a.nx : x);
+    int xm, xp;
+    side_columns(x, a.nx, xm, xp);
+    const uint32_t ux = (uint32_t)x * ES, uxm = (uint32_t)xm * ES, uxp = (uint32_t)xp * ES;
+    const bool out = lane >= 1 && lane <= nout;
+    // rows of the state at t + 1: the workgroup's and one on each side.  Beyond a
+    // wall there is none: the wall row is taken again, and what it sends is
+    // replaced by the bounce-back of the wall row's nodes.
+    auto row_of = [&](int r) {
+        const int lo = a.walls ? 0 : r + a.ny, hi = a.walls ? a.ny - 1 : r - a.ny;
+        return r < 0 ? lo : (r >= a.ny ? hi : r);
+    };
+    const uint32_t P = (uint32_t)a.istride * ES, row_bytes = 9u * P;
+    const auto fmap = buffer_of(flags, (uint32_t)a.ny * (uint32_t)a.opitch);
+    // the populations and the flag of the next row of the state at t + 1: its row
+    // and the rows below and above it, advanced by one row per load
+    T raw[9];
+    int fl, yp;
+    const T *pm, *p0, *pp;
+    uint32_t f0, fp;
+    auto start = [&](int r) {
+        yp = row_of(r + 1);
+        pm = fin + (int64_t)row_of(r - 1) * a.ystride;
+        p0 = fin + (int64_t)row_of(r) * a.ystride;
+        pp = fin + (int64_t)yp * a.ystride;
+        f0 = (uint32_t)row_of(r) * (uint32_t)a.opitch;
+        fp = (uint32_t)yp * (uint32_t)a.opitch;
+    };
+    auto load = [&]() {
+        const auto bm = buffer_of(pm, row_bytes), b0 = buffer_of(p0, row_bytes), bp = buffer_of(pp, row_bytes);
+        fl = __builtin_amdgcn_raw_buffer_load_b8(fmap, x, (int)f0, 0);
+        ld_buffer(raw[0], b0, ux, 0);
+        ld_buffer(raw[1], b0, uxm, P);
+        ld_buffer(raw[2], bm, ux, 2 * P);
+        ld_buffer(raw[3], b0, uxp, 3 * P);
+        ld_buffer(raw[4], bp, ux, 4 * P);
+        ld_buffer(raw[5], bm, uxm, 5 * P);
+        ld_buffer(raw[6], bm, uxp, 6 * P);
+        ld_buffer(raw[7], bp, uxp, 7 * P);
+        ld_buffer(raw[8], bp, uxm, 8 * P);
+        pm = p0;
+        p0 = pp;
+        f0 = fp;
+        if (yp + 1 < a.ny) {
+            ++yp;
+            pp += a.ystride;
+            fp += (uint32_t)a.opitch;
+        } else if (!a.walls) {
+            yp = 0;
+            pp = fin;
+            fp = 0;
+        }
+    };
+    // the state at t + 1 of the row before, and what the row before that sends up
+    T mine[9], up[3];
+#pragma unroll
+    for (int i = 0; i < 9; ++i) mine[i] = T(0);
+    up[0] = up[1] = up[2] = T(0);
+    int fl1 = kNodeSolid, fl_first = kNodeSolid;
+    // row y at t + 2, stored where `store` says, from its own state m, what the
+    // row below it sends up and the row above it down
+    auto finish = [&](int y, T* row, bool store, const T m[9], const T u[3], const T w[3], int flag) {
+        C d[9];
+        d[0] = Sto<T>::ld(m[0]);
+        d[1] = Sto<T>::ld(lane_before(m[1]));
+        d[3] = Sto<T>::ld(lane_after(m[3]));
+        d[2] = Sto<T>::ld(u[0]);
+        d[5] = Sto<T>::ld(u[1]);
+        d[6] = Sto<T>::ld(u[2]);
+        d[4] = Sto<T>::ld(w[0]);
+        d[7] = Sto<T>::ld(w[1]);
+        d[8] = Sto<T>::ld(w[2]);
+        if (flag == kNodeNear)
+            bounce_back<C>(d, xm, x, xp, y, own, vtab, a, [&](int j) -> C {
+                T v = m[1];
+#pragma unroll
+                for (int k = 2; k < 9; ++k) v = j == k ? m[k] : v;
+                return Sto<T>::ld(v);
+            });
+        collide<C>(d, cp);
+        const uint32_t at = store && out && flag != kNodeSolid ? ux : ~0u;
+        const auto to = buffer_of(row, row_bytes);
+#pragma unroll
+        for (int i = 0; i < 9; ++i) st_buffer(Sto<T>::st(d[i]), to, at, (uint32_t)i * P);
+    };
+    if (wave < nw) {
+        const int r0 = lowest ? ya - 1 : ya, r1 = highest ? yb : yb - 1;
+        T* row_out = fout + (int64_t)ya * a.ystride;
+        start(r0);
+        load();
+        {
+            // nine stores of nothing: every iteration then finds its row's loads
+            // followed by nine stores, and waits for the loads alone
+            const auto to = buffer_of(row_out, row_bytes);
+#pragma unroll
+            for (int i = 0; i < 9; ++i) st_buffer(T(0), to, ~0u, (uint32_t)i * P);
+        }
+#pragma unroll 1
+        for (int r = r0; r <= r1; ++r) {
+            // Row r of the state at t + 1.  Its loads were issued an iteration
+            // ago and are read here, before the next row's are issued to the
+            // same registers (the barriers).
+            C d[9];
+#pragma unroll
+            for (int i = 0; i < 9; ++i) d[i] = Sto<T>::ld(raw[i]);
+            int fr;
+            asm volatile("v_mov_b32 %0, %1"
+                         : "=v"(fr)
+                         : "v"(fl), "v"(d[0]), "v"(d[1]), "v"(d[2]), "v"(d[3]), "v"(d[4]), "v"(d[5]), "v"(d[6]),
+                           "v"(d[7]), "v"(d[8]));
+            __builtin_amdgcn_sched_barrier(0);
+            load();
+            __builtin_amdgcn_sched_barrier(0);
+            if (fr == kNodeNear) {
+                const T* row = fin + (int64_t)row_of(r) * a.ystride + x;
+                bounce_back<C>(d, xm, x, xp, row_of(r), own, vtab, a,
+                               [&](int j) -> C { return Sto<T>::ld(row[j * a.istride]); });
+            }
+            collide<C>(d, cp);
+            T g[9], down[3];
+#pragma unroll
+            for (int i = 0; i < 9; ++i) g[i] = Sto<T>::st(d[i]);
+            down[0] = g[4];
+            down[1] = lane_after(g[7]);
+            down[2] = lane_before(g[8]);
+            if (r == ya) {
+#pragma unroll
+                for (int i = 0; i < 3; ++i) sh.down[wave][i][lane] = down[i];
+            }
+            if (r == ya + 1 && !lowest) {
+                // the wave below has not reached the row under the first yet
+#pragma unroll
+                for (int i = 0; i < 9; ++i) sh.first[wave][i][lane] = mine[i];
+#pragma unroll
+                for (int i = 0; i < 3; ++i) sh.first[wave][9 + i][lane] = down[i];
+                fl_first = fl1;
+            }
+            finish(row_of(r - 1), row_out, r > (lowest ? ya : ya + 1), mine, up, down, fl1);
+            if (r > ya) row_out += a.ystride;
+            up[0] = mine[2];
+            up[1] = lane_before(mine[5]);
+            up[2] = lane_after(mine[6]);
+#pragma unroll
+            for (int i = 0; i < 9; ++i) mine[i] = g[i];
+            fl1 = fr;
+        }
+        // (the highest wave's last row is the one above its run)
+        if (!highest) {
+            sh.up[wave][0][lane] = mine[2];
+            sh.up[wave][1][lane] = lane_before(mine[5]);
+            sh.up[wave][2][lane] = lane_after(mine[6]);
+        }
+    }
+    __syncthreads();
+    if (wave >= nw) return;
+    // rows that waited for a neighbouring wave: the last of each run but the
+    // highest, the first of each but the lowest
+#pragma unroll 1
+    for (int k = highest ? 1 : 0; k < (lowest ? 1 : 2); ++k) {
+        T down[3];
+        const int y = k == 0 ? yb - 1 : ya, flag = k == 0 ? fl1 : fl_first;
+#pragma unroll
+        for (int i = 0; i < 3; ++i) down[i] = k == 0 ? sh.down[wave + 1][i][lane] : sh.first[wave][9 + i][lane];
+        if (k == 1) {
+#pragma unroll
+            for (int i = 0; i < 9; ++i) mine[i] = sh.first[wave][i][lane];
+#pragma unroll
+            for (int i = 0; i < 3; ++i) up[i] = sh.up[wave - 1][i][lane];
+        }
+        finish(y, fout + (int64_t)y * a.ystride, true, mine, up, down, flag);
+    }
+}
+
+// Work split of the two-step update: strips of `width` columns, runs of rows (run
+// k: rows ny k / runs on), one workgroup per strip and run.
+struct PairArgs {
+    int strips, width, runs;
+};
+
+// Two steps t -> t + 2: workgroups [0, n_force) the link forces of step t from
+// the stored state, the next n_force those of step t + 1 (each link's node is
+// taken one step on by its own thread), one that forms the totals of the launch
+// before and advances the step counter, and from n_lead on the update.
+template <typename T>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 3 : 4, 8))) void k_pair(
+    StepPtrs<T> p, const uint8_t* __restrict__ flags, int slot, RoleCounts rc, StepArgs sa, ForceArgs fa, PairArgs pa,
+    CollideParams<typename Sto<T>::C> cp) {
+    __shared__ union Shared {
+        ForceShared f;
+        PairShared<T> s;
+    } sh;
+    const int b = (int)blockIdx.x;
+    if (b < rc.n_lead) {
+        const int64_t t = p.tctr[slot];
+        if (b < rc.n_force) {
+            force_role<T, false>(b, sh.f, p.fin, p.own_t, p.links_t, p.seg_cnt_t, p.seg_off, p.chunk_solid,
+                                 p.chunk_start, p.sol, p.vtab, p.rtab, p.part(t, fa.nchunks), t, fa);
+        } else if (b < 2 * rc.n_force) {
+            force_role<T, false>(b - rc.n_force, sh.f, p.fin, p.own_t, p.links_t, p.seg_cnt_t, p.seg_off,
+                                 p.chunk_solid, p.chunk_start, p.sol, p.vtab, p.rtab, p.part(t + 1, fa.nchunks), t + 1,
+                                 fa, [&](int x, int y, int i) {
+                                     return next_pop<T>(p.fin, p.own_t, p.vtab, sa, cp, x, y, i);
+                                 });
+        } else if (b == 2 * rc.n_force) {
+            finalize_last(p, t, rc.n_fin, fa);
+            if (threadIdx.x == 0) p.tctr[slot ^ 1] = t + 2;
+        }
+        return;
+    }
+    // XCD k = j % 8 takes the runs k, k + 8, ...: neighbouring strips of a run
+    // share an L2, and the eight XCDs stay in one neighbourhood of rows
+    const uint32_t j = (uint32_t)(b - rc.n_lead), q = j >> 3;
+    const uint32_t group = q / (uint32_t)pa.strips;
+    const int run = (int)(group * 8u + (j & 7u)), strip = (int)(q - group * (uint32_t)pa.strips);
+    if (run >= pa.runs) return;
+    const int x0 = strip * pa.width;
+    const int nout = x0 + pa.width <= sa.nx ? pa.width : sa.nx - x0;
+    const int Ya = (int)((int64_t)sa.ny * run / pa.runs), Yb = (int)((int64_t)sa.ny * (run + 1) / pa.runs);
+    pair_strip<T>(sh.s, p.fin, p.fout, p.own_t, flags, p.vtab, x0, nout, Ya, Yb, sa, cp);
 }
 
 // Free bodies after the step: two workgroups per body (part 0: Newton-Euler

@@ -568,3 +568,52 @@ def test_mover_boxes_f64(oracle_mod, lbm_mod, nx, ny, walls, body):
     lat, osim = run_pair(oracle_mod, lbm_mod, c, 70)
     compare_fields(lat, osim, 1e-12)
     compare_forces(lat, osim, c, 1e-10)
+
+
+def _pair_case(nx, ny, walls, seed):
+    """A lattice with discs and boxes whose surfaces move (geometry fixed):
+    across the boundary of two strips and the periodic x boundary, near the
+    first and last rows, and rows of boxes that meet the boundaries of runs."""
+    rng = np.random.default_rng(seed)
+    bodies = []
+    if nx >= 56:
+        bodies = [lc.disc(0.45 * nx, 8.2, 4.6, vx=0.02, vy=-0.01), lc.disc(0.6 * nx, ny - 9.7, 5.1, vx=-0.03),
+                  lc.box(nx - 1.0, ny // 2, 2.0, 1.0, vy=0.02)]
+        bodies += [lc.box(20.0, ny // 3 + 9 * k, 3.0, 1.0, vx=0.01 * k) for k in range(5)]
+    g = rng.uniform(-1e-5, 1e-5, 2)
+    return lc.make_case(nx, ny, 0.7, walls_y=walls, gx=float(g[0]), gy=float(g[1]), u0=(0.03, -0.02),
+                        wall_v=(0.01, 0.0) if walls else (0.0, 0.0), bodies=bodies, name="pair")
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("mrt", [None, (1.64, 1.54, 1.9)])
+@pytest.mark.parametrize("walls", [False, True])
+def test_two_steps_per_launch_equal_single_steps(lbm_mod, dtype, mrt, walls):
+    """Lattices of fixed geometry take two steps per launch with the state
+    between in registers; the profiling mode takes one per launch.  Both give
+    the same populations and per-step forces bit for bit, at the edges of the
+    strips (62 columns) and of the runs of rows, for odd counts, blocks
+    replayed as graphs, and after a checkpoint."""
+    import torch
+
+    # (64 MiB of populations and more; rows padded to 64 nodes)
+    for nx, ny in ((5, 29130), (56, 29201), (57, 30000), (64, 29127), (65, 14571), (113, 15007), (250, 7303), (1000, 1899)):
+        c = _pair_case(nx, ny, walls, nx * 100 + ny)
+        _say(f"pair {nx}x{ny} {dtype} walls={walls} mrt={mrt is not None} bodies={len(c['bodies'])}")
+        a = lbm_mod.Lattice(c, dtype=dtype, history_steps=64, mrt=mrt)
+        b = lbm_mod.Lattice(c, dtype=dtype, history_steps=64, mrt=mrt)
+        b.profile(True)
+        for n in (2, 1, 35, 4):
+            a.step(n)
+            b.step(n)
+            assert bool((a.populations() == b.populations()).all()), (nx, ny, a.t)
+            assert bool((a.force_history() == b.force_history()).all()), (nx, ny, a.t)
+        r = lbm_mod.Lattice(c, dtype=dtype, history_steps=2, mrt=mrt)
+        r.load(a.save())
+        for lat in (a, b, r):
+            lat.step(5)
+        torch.cuda.synchronize()
+        assert bool((r.populations() == b.populations()).all())
+        assert bool((r.force_history(r.t - 2, 2) == b.force_history(b.t - 2, 2)).all())
+        del a, b, r
+        torch.cuda.empty_cache()
