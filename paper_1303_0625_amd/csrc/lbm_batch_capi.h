@@ -287,10 +287,10 @@ void batch_monitor_tw(lbm_batch* b, hipStream_t st, int k_steps, double tol) {
         k_batch_monitor<T, W><<<b->n_tiles, W * 64, 0, st>>>(
             bws<CaseDev>(b, b->o_cases), bws<Tile>(b, b->o_tiles), bws<int>(b, b->o_conv), bws<T>(b, b->o_f),
             bws<uint8_t>(b, b->o_own), bws<double>(b, b->o_snap), bws<double>(b, b->o_mpart), p);
-    k_batch_finalize<<<(b->n + 255) / 256, 256, 0, st>>>(
+    k_batch_finalize<<<b->n, kBlock, 0, st>>>(
         bws<CaseDev>(b, b->o_cases), bws<int>(b, b->o_tfirst), bws<int>(b, b->o_tcount),
         bws<double>(b, b->o_mpart), bws<BatchChunk>(b, b->o_chunks), bws<double>(b, b->o_fpart),
-        bws<CaseResult>(b, b->o_res), bws<int>(b, b->o_conv), bws<double>(b, b->o_forces), b->max_nsol, b->n,
+        bws<CaseResult>(b, b->o_res), bws<int>(b, b->o_conv), bws<double>(b, b->o_forces), b->max_nsol,
         bws<int64_t>(b, b->o_tdev), p, k_steps, tol);
 }
 

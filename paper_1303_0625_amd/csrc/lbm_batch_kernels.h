@@ -157,9 +157,12 @@ __global__ __launch_bounds__(WAVES * 64) void k_batch_monitor(const CaseDev* __r
     }
 }
 
-// One thread per case: residual from the tile partials (in tile order), force
-// totals per solid from the chunk partials (in chunk order); retire the case
-// when a previous snapshot exists and r < tol.
+// One workgroup per case: residual from the tile partials (thread j takes tiles
+// j, j + 256, ... in order, then a fixed tree), force totals per solid from the
+// chunk partials (in chunk order, one component per thread); retire the case
+// when a previous snapshot exists and r < tol.  (Bound by latency: one thread per
+// case walking its up to 2048 tile partials in turn took 747 us per check of 64
+// cases of up to 1024 x 512, four steps' worth.)
 struct CaseResult {
     int converged;
     int have_snap;
@@ -167,33 +170,45 @@ struct CaseResult {
     double residual;
 };
 
-__global__ void k_batch_finalize(const CaseDev* __restrict__ cases, const int* __restrict__ tile_first,
-                                 const int* __restrict__ tile_count, const double* __restrict__ mon_partial,
-                                 const BatchChunk* __restrict__ chunks,
-                                 const double* __restrict__ force_partial, CaseResult* __restrict__ res,
-                                 int* __restrict__ converged, double* __restrict__ forces, int max_nsol,
-                                 int n_cases, const int64_t* __restrict__ tdev, int parity, int k_steps,
-                                 double tol) {
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= n_cases) return;
+__global__ __launch_bounds__(kBlock) void k_batch_finalize(
+    const CaseDev* __restrict__ cases, const int* __restrict__ tile_first, const int* __restrict__ tile_count,
+    const double* __restrict__ mon_partial, const BatchChunk* __restrict__ chunks,
+    const double* __restrict__ force_partial, CaseResult* __restrict__ res, int* __restrict__ converged,
+    double* __restrict__ forces, int max_nsol, const int64_t* __restrict__ tdev, int parity, int k_steps, double tol) {
+    __shared__ double red[kBlock / 64][2];
+    const int c = (int)blockIdx.x;
     if (converged[c]) return;
     const CaseDev& cd = cases[c];
     double dd = 0.0, uu = 0.0;
-    for (int b = tile_first[c]; b < tile_first[c] + tile_count[c]; ++b) {
+    const int b1 = tile_first[c] + tile_count[c];
+    for (int b = tile_first[c] + (int)threadIdx.x; b < b1; b += kBlock) {
         dd += mon_partial[2 * (size_t)b];
         uu += mon_partial[2 * (size_t)b + 1];
     }
+    dd = wave_sum(dd);
+    uu = wave_sum(uu);
+    if ((threadIdx.x & 63) == 0) {
+        red[threadIdx.x >> 6][0] = dd;
+        red[threadIdx.x >> 6][1] = uu;
+    }
+    // chunks of a case are listed solid by solid: chunk order is summation order
+    double* fc = forces + (size_t)c * max_nsol * 6;
+    const int c1 = cd.chunk_first + cd.chunk_count;
+    for (int r = (int)threadIdx.x; r < cd.nsol * 6; r += kBlock) {
+        const int s = r / 6, q = r - 6 * s;
+        double v = 0.0;
+        for (int cc = cd.chunk_first; cc < c1; ++cc)
+            if (chunks[cc].s == s) v += force_partial[(size_t)cc * 6 + q];
+        fc[r] = v;
+    }
+    __syncthreads();  // (every thread has read the case's flag)
+    if (threadIdx.x != 0) return;
+    dd = (red[0][0] + red[1][0]) + (red[2][0] + red[3][0]);
+    uu = (red[0][1] + red[1][1]) + (red[2][1] + red[3][1]);
     // a state that is not finite (a diverged start) reports NaN and never retires
     const double r = !(isfinite(dd) && isfinite(uu))
                          ? __builtin_nan("")
                          : (uu > 0.0 ? sqrt(dd) / ((double)k_steps * sqrt(uu)) : (dd > 0.0 ? 1.0 : 0.0));
-    double* fc = forces + (size_t)c * max_nsol * 6;
-    for (int q = 0; q < cd.nsol * 6; ++q) fc[q] = 0.0;
-    // chunks of a case are listed solid by solid: chunk order is summation order
-    for (int cc = cd.chunk_first; cc < cd.chunk_first + cd.chunk_count; ++cc) {
-        const int s = chunks[cc].s;
-        for (int q = 0; q < 6; ++q) fc[s * 6 + q] += force_partial[(size_t)cc * 6 + q];
-    }
     CaseResult rr = res[c];
     rr.residual = rr.have_snap ? r : -1.0;
     rr.steps = tdev[parity];
