@@ -27,11 +27,15 @@ struct lbm_batch {
     int n_tiles_max = 0;
     // layout (byte offsets)
     size_t o_cases, o_tiles, o_conv, o_f, o_side, o_own, o_snap, o_links, o_segcnt, o_segoff, o_segcap, o_sol,
-        o_vtab, o_chunks, o_fpart, o_mpart, o_res, o_forces, o_tdev, o_tfirst, o_tcount, o_list, o_err;
+        o_vtab, o_chunks, o_fpart, o_mpart, o_res, o_forces, o_tdev, o_tfirst, o_tcount, o_list, o_err, o_flags,
+        o_ptiles;
     // current tiling
     int waves = 4;
     int nt = 1;
     int n_tiles = 0;
+    // two steps per launch (from kPairBytes of populations on): its workgroups
+    bool pairs = false;
+    int n_ptiles = 0;
     std::vector<int> conv_h;  // host copy of the converged flags (at the last sync)
     int64_t t = 0;
     int64_t last_snap_t = -1;
@@ -68,8 +72,10 @@ struct BatchLayout {
     std::vector<int> seg_off, seg_cap, solid_base;
     int max_nsol;
     int n_tiles_max;
+    int n_ptiles_max;
     size_t o_cases, o_tiles, o_conv, o_f, o_side, o_own, o_snap, o_links, o_segcnt, o_segoff, o_segcap, o_sol,
-        o_vtab, o_chunks, o_fpart, o_mpart, o_res, o_forces, o_tdev, o_tfirst, o_tcount, o_list, o_err;
+        o_vtab, o_chunks, o_fpart, o_mpart, o_res, o_forces, o_tdev, o_tfirst, o_tcount, o_list, o_err, o_flags,
+        o_ptiles;
 };
 
 const char* batch_layout(const lbm_grid* grids, const double* taus, const lbm_solid* solids,
@@ -78,6 +84,9 @@ const char* batch_layout(const lbm_grid* grids, const double* taus, const lbm_so
     if (!grids || !taus || !n_solids) return "grids, taus and n_solids must not be NULL";
     const size_t es = dtype_size(grids[0].dtype);
     int64_t elem_off = 0, own_off = 0, snap_off = 0, side_el = 0;
+    int64_t pop_el = 0;  // population elements of one buffer
+    int64_t units = 0;  // workgroups of the two-step update
+    int most = 0;       // of one run
     int links = 0, sbase = 0;
     B.max_nsol = 1;
     B.n_tiles_max = 0;
@@ -117,6 +126,7 @@ const char* batch_layout(const lbm_grid* grids, const double* taus, const lbm_so
         d.fa.nsol = n_solids[c] + 1;
         d.fa.nchunks = 0;
         const int64_t fel = 9 * (int64_t)g.ny * pitch;
+        pop_el += fel;
         elem_off = (elem_off + 127) / 128 * 128;  // 256-byte aligned rows for every storage size
         d.f_off[0] = elem_off;
         d.sa.nseg = pitch >> kRefShift;
@@ -148,6 +158,9 @@ const char* batch_layout(const lbm_grid* grids, const double* taus, const lbm_so
         d.wpr = pitch / 64;
         d.nwaves = g.ny * d.wpr;
         B.n_tiles_max += d.nwaves;  // one wave per tile at the finest tiling
+        d.pair = pair_args(g.nx, g.ny);
+        units += (int64_t)d.pair.strips * d.pair.runs;
+        most = std::max(most, d.pair.strips);
         // links and chunks: walls, then bodies
         int local = 0;
         d.chunk_first = (int)B.chunks.size();
@@ -198,6 +211,12 @@ const char* batch_layout(const lbm_grid* grids, const double* taus, const lbm_so
     take(B.o_tcount, 4 * (size_t)n);
     take(B.o_list, 4 * (size_t)B.max_nsol);
     take(B.o_err, 4);
+    // two steps per launch: node flags, and the workgroup table (eight lists, each
+    // at most one run longer than the shortest)
+    const bool pairs = es >= 4 && es * (size_t)pop_el >= kPairBytes;
+    B.n_ptiles_max = pairs ? (int)(8 * (units / 8 + most + 1)) : 0;
+    take(B.o_flags, pairs ? (size_t)own_off : 0);
+    take(B.o_ptiles, sizeof(PairTile) * (size_t)B.n_ptiles_max);
     B.total = off;
     return nullptr;
 }
@@ -216,7 +235,36 @@ int build_tiles(lbm_batch* b, std::vector<Tile>& tiles, std::vector<int>& first,
     return (int)tiles.size();
 }
 
+// Workgroups of the two-step update of the cases not yet converged.  The
+// hardware hands consecutive workgroups to the eight XCDs in turn: the runs of
+// rows go to eight lists, each next run to the shortest, so that the strips of a
+// run share an L2; the lists are interleaved and padded with empty entries.
+void build_pair_tiles(lbm_batch* b, std::vector<PairTile>& tiles) {
+    std::vector<PairTile> list[8];
+    for (int c = 0; c < b->n; ++c) {
+        if (b->conv_h[c]) continue;
+        const PairArgs& a = b->cd[c].pair;
+        for (int r = 0; r < a.runs; ++r) {
+            int k = 0;
+            for (int j = 1; j < 8; ++j)
+                if (list[j].size() < list[k].size()) k = j;
+            for (int s = 0; s < a.strips; ++s) list[k].push_back(PairTile{c, s, r, 0});
+        }
+    }
+    size_t n = 0;
+    for (const auto& l : list) n = std::max(n, l.size());
+    tiles.assign(8 * n, PairTile{-1, 0, 0, 0});
+    for (int k = 0; k < 8; ++k)
+        for (size_t i = 0; i < list[k].size(); ++i) tiles[8 * i + k] = list[k][i];
+}
+
 lbm_status upload_tiles(lbm_batch* b) {
+    std::vector<PairTile> ptiles;
+    if (b->pairs) build_pair_tiles(b, ptiles);
+    b->n_ptiles = (int)ptiles.size();
+    if (b->n_ptiles > 0)
+        BCHK(b, hipMemcpyAsync(b->ws + b->o_ptiles, ptiles.data(), sizeof(PairTile) * ptiles.size(),
+                               hipMemcpyHostToDevice, b->run_stream));
     std::vector<Tile> tiles;
     std::vector<int> first, count;
     b->n_tiles = build_tiles(b, tiles, first, count);
@@ -236,44 +284,77 @@ lbm_status upload_tiles(lbm_batch* b) {
 }
 
 template <typename T, bool NT, int W>
-void launch_batch_step(lbm_batch* b, hipStream_t st) {
-    const int p = (int)(b->t & 1);
+void launch_batch_step(lbm_batch* b, hipStream_t st, int p) {
     k_batch_step<T, NT, W><<<b->n_tiles, W * 64, 0, st>>>(
         bws<CaseDev>(b, b->o_cases), bws<Tile>(b, b->o_tiles), bws<int>(b, b->o_conv), bws<T>(b, b->o_f),
         bws<uint8_t>(b, b->o_own), bws<double>(b, b->o_vtab), p, bws<int64_t>(b, b->o_tdev));
 }
 
 template <typename T, bool NT>
-void batch_step_w(lbm_batch* b, hipStream_t st) {
+void batch_step_w(lbm_batch* b, hipStream_t st, int p) {
     switch (b->waves) {
-        case 1: launch_batch_step<T, NT, 1>(b, st); break;
-        case 2: launch_batch_step<T, NT, 2>(b, st); break;
-        case 8: launch_batch_step<T, NT, 8>(b, st); break;
-        default: launch_batch_step<T, NT, 4>(b, st); break;
+        case 1: launch_batch_step<T, NT, 1>(b, st, p); break;
+        case 2: launch_batch_step<T, NT, 2>(b, st, p); break;
+        case 8: launch_batch_step<T, NT, 8>(b, st, p); break;
+        default: launch_batch_step<T, NT, 4>(b, st, p); break;
     }
 }
 
 template <typename T>
-void batch_step_t(lbm_batch* b, hipStream_t st) {
+void batch_step_t(lbm_batch* b, hipStream_t st, int p) {
     if (b->nt)
-        batch_step_w<T, true>(b, st);
+        batch_step_w<T, true>(b, st, p);
     else
-        batch_step_w<T, false>(b, st);
+        batch_step_w<T, false>(b, st, p);
 }
 
-void batch_step_one(lbm_batch* b, hipStream_t st) {
+template <typename T>
+void launch_batch_pair(lbm_batch* b, hipStream_t st, int p) {
+    k_batch_pair<T><<<b->n_ptiles, kBlock, 0, st>>>(
+        bws<CaseDev>(b, b->o_cases), bws<PairTile>(b, b->o_ptiles), bws<int>(b, b->o_conv), bws<T>(b, b->o_f),
+        bws<uint8_t>(b, b->o_own), bws<uint8_t>(b, b->o_flags), bws<double>(b, b->o_vtab), p,
+        bws<int64_t>(b, b->o_tdev));
+}
+
+// One step from buffer p (the parity of t unless an odd number of double steps
+// went before it in this call).
+void batch_step_from(lbm_batch* b, hipStream_t st, int p) {
     if (b->n_tiles > 0) {
         switch (b->dtype) {
-            case LBM_F64: batch_step_t<double>(b, st); break;
-            case LBM_F32: batch_step_t<float>(b, st); break;
-            case LBM_F16: batch_step_t<_Float16>(b, st); break;
-            default: batch_step_t<bf16_t>(b, st); break;
+            case LBM_F64: batch_step_t<double>(b, st, p); break;
+            case LBM_F32: batch_step_t<float>(b, st, p); break;
+            case LBM_F16: batch_step_t<_Float16>(b, st, p); break;
+            default: batch_step_t<bf16_t>(b, st, p); break;
         }
     } else {
         // every case retired: keep the step counter moving
         k_set_counters<<<1, 1, 0, st>>>(bws<int64_t>(b, b->o_tdev), b->t + 1, bws<int>(b, b->o_err));
     }
     b->t += 1;
+}
+
+void batch_step_one(lbm_batch* b, hipStream_t st) { batch_step_from(b, st, (int)(b->t & 1)); }
+
+// n steps.  Every launch, of one step or of two, reads one buffer and writes the
+// other; an even number of double steps leaves the state in the buffer of t's
+// parity, where every reader looks.
+void batch_steps(lbm_batch* b, hipStream_t st, int64_t n) {
+    int64_t two = b->n_ptiles > 0 ? n / 4 * 2 : 0;
+    int p = (int)(b->t & 1);
+    for (int64_t k = 0; k < n; p ^= 1) {
+        if (two > 0) {
+            if (b->dtype == LBM_F64)
+                launch_batch_pair<double>(b, st, p);
+            else
+                launch_batch_pair<float>(b, st, p);
+            b->t += 2;
+            k += 2;
+            --two;
+        } else {
+            batch_step_from(b, st, p);
+            k += 1;
+        }
+    }
 }
 
 template <typename T, int W>
@@ -492,6 +573,9 @@ lbm_status lbm_batch_create(const lbm_grid* grids, const double* taus, const lbm
     b->o_fpart = B.o_fpart; b->o_mpart = B.o_mpart; b->o_res = B.o_res; b->o_forces = B.o_forces;
     b->o_tdev = B.o_tdev; b->o_tfirst = B.o_tfirst; b->o_tcount = B.o_tcount; b->o_list = B.o_list;
     b->o_err = B.o_err;
+    b->o_flags = B.o_flags;
+    b->o_ptiles = B.o_ptiles;
+    b->pairs = B.n_ptiles_max > 0;
     b->conv_h.assign(n_cases, 0);
     b->err[0] = 0;
     // the working set decides the streaming mode of the update
@@ -553,6 +637,9 @@ lbm_status lbm_batch_create(const lbm_grid* grids, const double* taus, const lbm
         const int nb = d.nsol - 1;
         const SolidDev* sd = bws<SolidDev>(b, b->o_sol) + d.solid_base;
         if (nb > 0) k_raster<<<nb, kBlock, 0, st>>>(own, sd, bws<int>(b, b->o_list), 0, ga);
+        if (b->pairs)
+            k_node_flags<<<(unsigned)(((int64_t)g.ny * d.sa.rowlen + kBlock - 1) / kBlock), kBlock, 0, st>>>(
+                own, bws<uint8_t>(b, b->o_flags) + d.own_off, d.sa);
         uint32_t* L = bws<uint32_t>(b, b->o_links) + d.links_base;
         if (g.walls_y) k_wall_links<<<(2 * g.nx + 255) / 256, 256, 0, st>>>(L, g.nx, g.ny);
         if (nb > 0) {
@@ -590,7 +677,7 @@ lbm_status lbm_batch_step(lbm_batch* b, int64_t n) {
     if (!b || n < 0) return LBM_EINVAL;
     lbm_status rs = batch_join_user(b);
     if (rs != LBM_OK) return rs;
-    for (int64_t k = 0; k < n; ++k) batch_step_one(b, b->run_stream);
+    batch_steps(b, b->run_stream, n);
     BCHK(b, hipGetLastError());
     BCHK(b, hipStreamSynchronize(b->run_stream));
     return LBM_OK;
@@ -645,7 +732,7 @@ lbm_status lbm_batch_run(lbm_batch* b, int64_t max_steps, double tol, int32_t ch
             hipGraph_t g;
             const int64_t tsave = b->t;
             BCHK(b, hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
-            for (int s = 0; s < k; ++s) batch_step_one(b, st);
+            batch_steps(b, st, k);
             batch_monitor_one(b, st, k, tol);
             b->t = tsave;
             BCHK(b, hipStreamEndCapture(st, &g));
@@ -659,7 +746,7 @@ lbm_status lbm_batch_run(lbm_batch* b, int64_t max_steps, double tol, int32_t ch
             BCHK(b, hipGraphLaunch(b->gexec, st));
             b->t += k;
         } else {
-            for (int s = 0; s < k; ++s) batch_step_one(b, st);
+            batch_steps(b, st, k);
             batch_monitor_one(b, st, k, tol);
         }
         b->last_snap_t = b->t;

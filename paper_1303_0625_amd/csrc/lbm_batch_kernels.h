@@ -27,6 +27,7 @@ struct CaseDev {
     int chunk_first, chunk_count;  // force chunks of the case
     int wpr;                // waves per row (rowlen / 64)
     int nwaves;             // ny * wpr
+    PairArgs pair;          // split of the two-step update
 };
 
 // Update tile: `waves` consecutive waves of one case, starting at wave0.
@@ -68,6 +69,33 @@ __global__ __launch_bounds__(WAVES * 64) void k_batch_step(const CaseDev* __rest
     }
     step_node<T, NT>(x, y, fbase + cd.f_off[parity], fbase + cd.f_off[parity ^ 1], obase + cd.own_off,
                      vtab_all + 2 * cd.solid_base, nullptr, nullptr, 0, cd.sa, case_cp<T>(cd), nullptr, x < cd.sa.nx);
+}
+
+// Two time steps of every listed workgroup of the two-step update (strip and run
+// of a case; c < 0: none); a case marked converged is skipped.  slot: the buffer
+// read, toggled by every launch, as is the slot of the step counter.
+struct PairTile {
+    int c, strip, run, pad;
+};
+
+template <typename T>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 3 : 4, 8))) void k_batch_pair(
+    const CaseDev* __restrict__ cases, const PairTile* __restrict__ tiles, const int* __restrict__ converged,
+    T* __restrict__ fbase, const uint8_t* __restrict__ obase, const uint8_t* __restrict__ flags,
+    const double* __restrict__ vtab_all, int slot, int64_t* __restrict__ tdev) {
+    __shared__ PairShared<T> sh;
+    const PairTile tl = tiles[blockIdx.x];
+    if (blockIdx.x == 0 && threadIdx.x == 0) tdev[slot ^ 1] = tdev[slot] + 2;
+    if (tl.c < 0 || converged[tl.c]) return;
+    const CaseDev& cd = cases[tl.c];
+    // (copies: scalars held through the loop over rows)
+    const StepArgs sa = cd.sa;
+    const CollideParams<double> cp = cd.cp64;
+    const PairArgs pa = cd.pair;
+    const int x0 = tl.strip * pa.width, nout = x0 + pa.width <= sa.nx ? pa.width : sa.nx - x0;
+    const int Ya = (int)((int64_t)sa.ny * tl.run / pa.runs), Yb = (int)((int64_t)sa.ny * (tl.run + 1) / pa.runs);
+    pair_strip<T>(sh, fbase + cd.f_off[slot], fbase + cd.f_off[slot ^ 1], obase + cd.own_off, flags + cd.own_off,
+                  vtab_all + 2 * cd.solid_base, x0, nout, Ya, Yb, sa, cp);
 }
 
 // Force chunks of every active case at the current state (parity).

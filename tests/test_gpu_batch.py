@@ -314,3 +314,46 @@ def test_set_active_retires_and_resumes_across_parity(lbm_mod):
         (rho, ux, uy), _ = lone_state(lbm_mod, case, "f64", steps)
         got = [_np(a) for a in batch.fields(k, "f64")]
         assert np.array_equal(got[0], rho) and np.array_equal(got[1], ux) and np.array_equal(got[2], uy), k
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+def test_large_batch_takes_two_steps_per_launch(lbm_mod, dtype):
+    """A batch of 64 MiB of populations and more takes two steps per launch
+    (an even number of times per call, the rest singly): every case equals a
+    lone lattice stepped singly bit for bit, for step counts of every remainder,
+    through check intervals replayed as graphs or launched one by one, and with
+    cases retired."""
+    shapes = [(1001, 517), (57, 1200), (1024, 900), (130, 700), (64, 5), (600, 411)]
+    cases = []
+    for k, (nx, ny) in enumerate(shapes):
+        bodies = [lc.disc(0.4 * nx, 0.5 * ny, 4.3 + k, vx=0.01)] if ny > 40 else []
+        cases.append(lc.make_case(nx, ny, 0.6 + 0.05 * k, walls_y=k % 2 == 0, gx=2e-6, u0=(0.02, 0.01), bodies=bodies,
+                                  name=f"pair_batch_{k}"))
+    b = lbm_mod.LatticeBatch(cases, dtype=dtype)
+    lone = [lbm_mod.Lattice(c, dtype=dtype, history_steps=4) for c in cases]
+    for lat in lone:
+        lat.profile(True)
+
+    def same(batch):
+        for k, lat in enumerate(lone):
+            for x, y in zip(batch.fields(k), lat.fields()[:3]):
+                assert bool((x == y).all()), (cases[k]["name"], lat.t)
+
+    for n in (1, 2, 3, 4, 6, 9):
+        b.step(n)
+        for lat in lone:
+            lat.step(n)
+        same(b)
+    plain = lbm_mod.LatticeBatch(cases, dtype=dtype)
+    plain.set_graph(False)
+    plain.step(25)
+    for batch in (b, plain):
+        batch.set_active(2, False)
+        assert batch.run(30, 1e-30, 10) == 30
+        batch.set_active(2, True)
+        batch.step(5)
+    for k, lat in enumerate(lone):
+        lat.step(5 if k == 2 else 35)
+    same(b)
+    same(plain)
+    assert b.status()[2:] == plain.status()[2:]
