@@ -538,7 +538,7 @@ lbm_status enqueue_step(lbm_ctx* c) {
         fr.rho0 = c->g.rho0;
         fr.scheme = c->dyn_scheme == LBM_CME ? 0 : 1;
         auto kf = c->mrt ? k_free<T, true> : k_free<T, false>;
-        kf<<<2 * n_free, kBlock, 2 * (size_t)c->L.box_bytes, c->stream>>>(fp, p, fm, fr, cp);
+        kf<<<2 * n_free, kFreeBlock, 2 * (size_t)c->L.box_bytes, c->stream>>>(fp, p, fm, fr, cp);
     }
     c->t += 1;
     c->cur ^= 1;

@@ -1017,7 +1017,8 @@ struct MoveShared {
 // Mover role m: part m / n_movers for body movers[m % n_movers]; lds holds
 // the two byte maps (2 * box_bytes).  GEO: link geometry in the refill
 // stencil (spinning free bodies, interpolated bounce-back).
-template <typename T, bool MRT, bool GEO>
+// BLOCK: threads of the workgroup.
+template <typename T, bool MRT, bool GEO, int BLOCK = kBlock>
 __device__ inline void move_role(int m, uint8_t* __restrict__ lds, MoveShared<T>& sm,
                                  const T* __restrict__ fin, T* __restrict__ fout,
                                  const uint8_t* __restrict__ own_t, uint8_t* __restrict__ own_n,
@@ -1109,10 +1110,10 @@ __device__ inline void move_role(int m, uint8_t* __restrict__ lds, MoveShared<T>
         const int qy = q / W;
         return at_xy(q - qy * W, qy, gx, gy);
     };
-    // a thread walks the box nodes threadIdx.x, threadIdx.x + kBlock, ...: its
+    // a thread walks the box nodes threadIdx.x, threadIdx.x + BLOCK, ...: its
     // column and row advance without a division per node
     const int row0 = (int)threadIdx.x / W, col0 = (int)threadIdx.x - row0 * W;
-    const int drow = kBlock / W, dcol = kBlock - drow * W;
+    const int drow = BLOCK / W, dcol = BLOCK - drow * W;
     auto next_node = [&](int& qx, int& qy) {
         qx += dcol;
         qy += drow;
@@ -1132,7 +1133,7 @@ __device__ inline void move_role(int m, uint8_t* __restrict__ lds, MoveShared<T>
         constexpr int R = 4;
         int qx = col0, qy = row0;
         const double xd = (double)x0, yd = (double)y0;  // (exact sums: the node's integer coordinates)
-        for (int q0 = 0; q0 < N; q0 += R * kBlock) {
+        for (int q0 = 0; q0 < N; q0 += R * BLOCK) {
             uint8_t vt[R], vn[R];
             uint32_t o[R];
             uint32_t outside = 0;
@@ -1154,7 +1155,7 @@ __device__ inline void move_role(int m, uint8_t* __restrict__ lds, MoveShared<T>
             qy = qy0;
 #pragma unroll
             for (int r = 0; r < R; ++r) {
-                const int q = q0 + r * kBlock + (int)threadIdx.x;
+                const int q = q0 + r * BLOCK + (int)threadIdx.x;
                 const bool wall = (outside >> r & 1u) != 0u;
                 const uint8_t v = wall ? kWallMark : vn[r], ov = wall ? kWallMark : vt[r];
                 const bool in = solid_inside(S, Xn, Yn, xd + (double)qx, yd + (double)qy);
@@ -1179,7 +1180,7 @@ __device__ inline void move_role(int m, uint8_t* __restrict__ lds, MoveShared<T>
     }
     __syncthreads();
     // 3. link list of G_{t+1}, row-major (y, x, i) over the box interior.  Wave w
-    // takes the groups of 64 consecutive nodes w, w + 4, ...: each lane marks
+    // of n takes the groups of 64 consecutive nodes w, w + n, ...: each lane marks
     // its node's directions into the body as bits (kept in place of the owners
     // of G_t, which part 0 does not stage); a link's place is the number of
     // links in the groups before, plus that of the lanes before in its own
@@ -1192,7 +1193,7 @@ __device__ inline void move_role(int m, uint8_t* __restrict__ lds, MoveShared<T>
         const int ngrp = (N + 63) / 64;
         {
             int qx = col0, qy = row0;
-            for (int q = threadIdx.x; q - lane < N; q += kBlock, next_node(qx, qy)) {
+            for (int q = threadIdx.x; q - lane < N; q += BLOCK, next_node(qx, qy)) {
                 uint32_t bits = 0;
                 if (q < N && qx != 0 && qy != 0 && qx != W - 1 && qy != H - 1) {
                     uint8_t nb[8];
@@ -1231,7 +1232,7 @@ __device__ inline void move_role(int m, uint8_t* __restrict__ lds, MoveShared<T>
         if (total <= cap) {
             uint32_t* L = links_n + soff;
             int qx = col0, qy = row0;
-            for (int q = threadIdx.x; q - lane < N; q += kBlock, next_node(qx, qy)) {
+            for (int q = threadIdx.x; q - lane < N; q += BLOCK, next_node(qx, qy)) {
                 const uint32_t bits = q < N ? ot[q] : 0u;
                 if (__ballot(bits != 0u) == 0ull) continue;
                 uint32_t before = (uint32_t)gtot[q >> 6];
@@ -1282,7 +1283,7 @@ __device__ inline void move_role(int m, uint8_t* __restrict__ lds, MoveShared<T>
         }
         __syncthreads();
         // 4b. post-advection values at the stencil nodes, in parallel
-        for (int w = threadIdx.x; w < nbat * 216; w += kBlock) {
+        for (int w = threadIdx.x; w < nbat * 216; w += BLOCK) {
             const int bb = w / 216, r = w % 216;
             const int k = r / 27 + 1, mm = (r % 27) / 9 + 1, j = r % 9;
             const int use = sm.nb_use[bb][k - 1];
@@ -2129,15 +2130,19 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T
 
 // Free bodies after the step: two workgroups per body (part 0: Newton-Euler
 // step, G_{t+1} and links; part 1: the same step and rasterisation, then the
-// newborn refill).  p.movers lists the free bodies.
+// newborn refill).  p.movers lists the free bodies.  Nothing else runs beside
+// them, and their chains are bound by latency: sixteen waves walk a body's box in
+// a quarter of the rounds of four (one disc in a 1200x120 channel: 10.5 us with
+// four waves, 8.6 with sixteen).
+constexpr int kFreeBlock = 1024;
 template <typename T, bool MRT>
-__global__ __launch_bounds__(kBlock) void k_free(StepPtrs<T> p, int parity, MoveArgs ma, FreeArgs fa,
-                                                 CollideParams<typename Sto<T>::C> cp) {
+__global__ __launch_bounds__(kFreeBlock) void k_free(StepPtrs<T> p, int parity, MoveArgs ma, FreeArgs fa,
+                                                     CollideParams<typename Sto<T>::C> cp) {
     extern __shared__ __align__(16) uint8_t dyn_lds[];
     __shared__ MoveShared<T> sm;
-    move_role<T, MRT, true>((int)blockIdx.x, dyn_lds, sm, p.fin, p.fout, p.own_t, p.own_n, p.links_n, p.seg_cnt_n,
-                      p.seg_off, p.seg_cap, p.sol, p.vtab, p.rtab, p.movers, p.tctr, parity, ma, cp, p.errflag,
-                      &fa);
+    move_role<T, MRT, true, kFreeBlock>((int)blockIdx.x, dyn_lds, sm, p.fin, p.fout, p.own_t, p.own_n, p.links_n,
+                                        p.seg_cnt_n, p.seg_off, p.seg_cap, p.sol, p.vtab, p.rtab, p.movers, p.tctr,
+                                        parity, ma, cp, p.errflag, &fa);
 }
 
 // Per-link force records of the current state (test and inspection path).
