@@ -919,7 +919,9 @@ lbm_status lbm_warm_check(int32_t nx, int32_t ny, int32_t n_fields, const uint8_
     }
     const hipStream_t st = (hipStream_t)hip_stream;
     k_fill_i32<<<blocks(n_fields), kEw, 0, st>>>(d_ok, n_fields, 1);
-    k_warm_check<<<n_fields, kEw, 0, st>>>(d_owner, d_rho, d_ux, d_uy, nx, ny, rho0, u_max, d_ok);
+    const unsigned runs = (unsigned)std::min<int64_t>(((int64_t)nx * ny + kEw * kWarmNodes - 1) / (kEw * kWarmNodes),
+                                                      kWarmRuns);
+    k_warm_check<<<dim3(n_fields, runs), kEw, 0, st>>>(d_owner, d_rho, d_ux, d_uy, nx, ny, rho0, u_max, d_ok);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) {
         nn_set_err(g_nn_err, "start check launch failed: %s", hipGetErrorString(e));

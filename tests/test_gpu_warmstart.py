@@ -95,3 +95,25 @@ def test_bad_learned_fields_fall_back_to_cold_start(torch_mod):
     assert 0 in b.fallback
     res = b.status()[2]
     assert all(np.isfinite(r) for r in res)
+
+
+@pytest.mark.parametrize("nx,ny", [(1, 1), (7, 5), (32, 32), (41, 25), (257, 129), (400, 200)])
+def test_warm_check_finds_a_bad_node_anywhere(nx, ny):
+    """One bad node per field set, at the first and last node and at the ends of
+    a thread's and a workgroup's run: its set alone is refused."""
+    import torch
+
+    from paper_1303_0625_amd import lbm
+
+    lbm.load_library()
+    n = nx * ny
+    places = sorted({0, n - 1, n // 2, min(255, n - 1), min(256, n - 1), min(1023, n - 1), min(1024, n - 1)})
+    k = len(places) + 1
+    own = torch.zeros((k, n), dtype=torch.uint8, device="cuda")
+    f = [torch.full((k, n), v, dtype=torch.float32, device="cuda") for v in (1.0, 0.01, 0.0)]
+    for j, q in enumerate(places):
+        f[j % 3][j, q] = float("nan") if j % 2 else 9.0
+        own[k - 1, q] = 1  # the last set's bad nodes are solid
+        f[j % 3][k - 1, q] = float("inf")
+    ok = lbm.warm_check(own.view(k, ny, nx), *(t.view(k, ny, nx) for t in f)).cpu().tolist()
+    assert ok == [0] * len(places) + [1]
