@@ -264,27 +264,25 @@ void conv(lbm_nn* n, int level, const void* in, int in_cs, int cin, const void* 
     a.W = p.W >> level;
     a.P = (int)((int64_t)n->batch * a.H * a.W);
     a.out_f32 = sizeof(OT) == 4 ? 1 : 0;
-    if (sizeof(T) == 2 && cin % 32 == 0 && a.H % kC9Rows == 0 && a.W % 32 == 0) {
+    a.vec = 0;
+    if (sizeof(T) == 2 && (cin % 32 == 0 || cin == 16) && a.H % kC9Rows == 0 && a.W % 32 == 0 &&
+        (int64_t)(kC9Rows + 2) * a.W * in_cs < (1 << 30)) {
         // BF16 with the input tile held across the nine taps, when the
         // launch still gives >= 256 workgroups
-        // (with <= 640 workgroups and several chunks the next chunk is
-        // prefetched into registers: fewer waves, but its loads overlap)
         const int64_t tiles = (int64_t)n->batch * (a.H / kC9Rows) * (a.W / 32);
-        const bool deep = cin >= 128;
-        if (cout_pad % 64 == 0 && tiles * (cout_pad / 64) >= 512) {
-            const dim3 g((unsigned)tiles, cout_pad / 64);
-            if (deep && tiles * (cout_pad / 64) <= 640)
-                k_conv9<2, true><<<g, 256, 0, n->st>>>(a);
-            else
-                k_conv9<2, false><<<g, 256, 0, n->st>>>(a);
+        auto wide = [&](const void* q, int cs, int co) { return cs % 8 == 0 && co % 8 == 0 && (uintptr_t)q % 16 == 0; };
+        a.vec = !a.out_f32 && cout == cout_pad && wide(out, out_cs, out_co) && (!mask || wide(mask, mask_cs, mask_co));
+        const dim3 g1((unsigned)tiles, cout_pad / 32), g2((unsigned)tiles, cout_pad / 64);
+        if (cin == 16) {
+            if (tiles * (cout_pad / 32) >= 256) {
+                k_conv9<1, 1><<<g1, 256, 0, n->st>>>(a);
+                return;
+            }
+        } else if (cout_pad % 64 == 0 && tiles * (cout_pad / 64) >= 512) {
+            k_conv9<2, 2><<<g2, 256, 0, n->st>>>(a);
             return;
-        }
-        if (tiles * (cout_pad / 32) >= 256) {
-            const dim3 g((unsigned)tiles, cout_pad / 32);
-            if (deep && tiles * (cout_pad / 32) <= 640)
-                k_conv9<1, true><<<g, 256, 0, n->st>>>(a);
-            else
-                k_conv9<1, false><<<g, 256, 0, n->st>>>(a);
+        } else if (tiles * (cout_pad / 32) >= 256) {
+            k_conv9<1, 2><<<g1, 256, 0, n->st>>>(a);
             return;
         }
     }

@@ -27,6 +27,7 @@ namespace nn {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kConvWaves = 4;  // waves per convolution workgroup
@@ -96,6 +97,7 @@ struct ConvArgs {
     int relu;
     int P, H, W;           // P = B * H * W pixels of this level
     int out_f32;           // k_conv_lds: store the output as float (network head)
+    int vec;               // k_conv9: whole blocks of BF16 channels at 16-byte addresses
 };
 
 // Workgroup: kConvWaves waves; wave w takes pixels
@@ -313,25 +315,53 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 3))) voi
 
 // 3x3 convolution with the input tile held across the nine taps (BF16).  A
 // workgroup computes an output tile of kC9Rows rows x 32 pixels of one image
-// for 32 NB output channels; per 32-channel chunk of the input it stages in
+// for 32 NB output channels; per chunk of 16 KS input channels it stages in
 // LDS the tile's input with a one-pixel halo (rows y0 - 1 .. y0 + kC9Rows,
 // columns x0 - 1 .. x0 + 32, x periodic, rows outside the image zero) and
 // the chunk's weights of all nine taps, so each input value is read from
 // memory once per chunk instead of once per tap.  Wave w takes output rows
 // 2w and 2w + 1; the operand of tap (dy, dx) for output pixel (r, m) is the
 // staged pixel (r + 1 + dy, m + 1 + dx): 8 consecutive channels, one aligned
-// 16-byte LDS vector.  Same epilogue as k_conv_lds.  Needs H % kC9Rows == 0,
-// W % 32 == 0, cin % 32 == 0 and cout_pad % (32 NB) == 0.
+// 16-byte LDS vector, kept for the next dy, where it is the other row's.
+// Sums run over chunks, taps, channels.  Same arguments as k_conv_lds.  Needs
+// H % kC9Rows == 0, W % 32 == 0, cin % (16 KS) == 0 and cout_pad % (32 NB) == 0.
+//
+// Bound by the latency of the staging loads (LDS reads take a sixth of the
+// time, the products a quarter).  A chunk's loads are therefore issued
+// together, before the products of the chunk in front of it, through buffer
+// descriptors: one offset register per input unit, none per weight unit, rows
+// outside the image out of range (zero).  That keeps two (NB = 2) and three
+// (NB = 1) workgroups on a compute unit; the products put channels in rows,
+// so that a lane holds runs of four channels and the tile leaves through LDS
+// in 16-byte stores.  256x128, batch 32, in us, before (loads waited for one by
+// one, or a prefetch that left one workgroup on a unit; two-byte stores) and
+// now: 16 -> 32 channels 77, 26 (k_conv_lds before); 32 -> 32 61, 41; 96 -> 32
+// 141, 91; 192 -> 64 at half size 106, 69; 640 -> 128 at quarter size 151, 103
+// (940 TFLOP/s).
 constexpr int kC9Rows = 8;
-constexpr int kC9Pitch = 40;  // LDS elements per staged pixel / weight row (32 + 8 pad)
 
-template <int NB, bool PF>
-__global__ __launch_bounds__(256) void k_conv9(ConvArgs a) {
+// Descriptor of `bytes` bytes from p (the same in every lane); loads from
+// beyond them give zero.
+__device__ inline __amdgpu_buffer_rsrc_t buffer_of(const __bf16* p, int bytes) {
+    const uint64_t u = reinterpret_cast<uint64_t>(p);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)u);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(u >> 32));
+    return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>((uint64_t)hi << 32 | lo), 0, bytes, 0x00020000);
+}
+
+template <int NB, int KS>
+__global__ __launch_bounds__(256, NB == 1 ? 3 : 2) void k_conv9(ConvArgs a) {
     constexpr int IR = kC9Rows + 2, IX = 34;         // staged input rows, pixels
-    constexpr int IN_UNITS = IR * IX * 4;            // 16-byte units (8 channels)
-    constexpr int W_UNITS = 32 * NB * 9 * 4;
-    __shared__ __align__(16) __bf16 Is[IR * IX * kC9Pitch];
-    __shared__ __align__(16) __bf16 Ws[32 * NB * 9 * kC9Pitch];
+    constexpr int UPP = 2 * KS;                      // 16-byte units (8 channels) per pixel or weight row
+    constexpr int PITCH = 16 * KS + 8;               // LDS elements per staged pixel / weight row
+    constexpr int IN_UNITS = IR * IX * UPP;
+    constexpr int W_UNITS = 32 * NB * 9 * UPP;
+    constexpr int IN_PER = (IN_UNITS + 255) / 256, W_PER = (W_UNITS + 255) / 256;
+    constexpr int kOutPitch = 32 * NB + 8;           // LDS elements per output pixel on the way out
+    constexpr int STAGE = (IR * IX + 32 * NB * 9) * PITCH, OUT = kC9Rows * 32 * kOutPitch;
+    __shared__ __align__(16) __bf16 lds[STAGE > OUT ? STAGE : OUT];
+    __bf16* const Is = lds;
+    __bf16* const Ws = lds + IR * IX * PITCH;
     const int t = threadIdx.x;
     const int l = t & 63, wave = t >> 6;
     const int kg = l >> 5;
@@ -343,9 +373,44 @@ __global__ __launch_bounds__(256) void k_conv9(ConvArgs a) {
     const int b = tile / nrow;
     const int x0 = seg * 32, y0 = rb * kC9Rows;
     const int nbase = blockIdx.y * 32 * NB;
-    const __bf16* in = static_cast<const __bf16*>(a.in);
-    const __bf16* w = static_cast<const __bf16*>(a.w);
-    const int wrow = 9 * a.cin;
+    // the tile's rows of the image and the workgroup's rows of weights
+    const int ya = y0 > 0 ? y0 - 1 : 0, yb = y0 + kC9Rows < a.H ? y0 + kC9Rows : a.H - 1;
+    const __amdgpu_buffer_rsrc_t rin_ = buffer_of(static_cast<const __bf16*>(a.in) + (int64_t)(b * a.H + ya) * a.W * a.in_cs,
+                                  2 * (((yb - ya + 1) * a.W - 1) * a.in_cs + a.cin));
+    const __amdgpu_buffer_rsrc_t rw_ = buffer_of(static_cast<const __bf16*>(a.w) + (int64_t)nbase * 9 * a.cin, 32 * NB * 9 * 2 * a.cin);
+    uint32_t oin[IN_PER];
+#pragma unroll
+    for (int k = 0; k < IN_PER; ++k) {
+        const int u = t + 256 * k;
+        const int q = u / UPP, px = q % IX, yy = y0 - 1 + q / IX;
+        int xx = x0 - 1 + px;
+        xx = xx < 0 ? xx + a.W : (xx >= a.W ? xx - a.W : xx);
+        const bool ok = u < IN_UNITS && yy >= 0 && yy < a.H;
+        oin[k] = ok ? 2u * (uint32_t)(((yy - ya) * a.W + xx) * a.in_cs + 8 * (u % UPP)) : 0x80000000u;
+    }
+    const uint32_t ow = 2u * (uint32_t)(t / UPP * a.cin + 8 * (t % UPP));
+    const int wstep = 256 / UPP * 2 * a.cin;         // bytes between a thread's weight units
+    const int ldst = t / UPP * PITCH + 8 * (t % UPP);
+    u32x4 vin[IN_PER], vw[W_PER];
+    auto load = [&](int c0) {
+#pragma unroll
+        for (int k = 0; k < IN_PER; ++k) vin[k] = __builtin_amdgcn_raw_buffer_load_b128(rin_, oin[k], 2 * c0, 0);
+#pragma unroll
+        for (int k = 0; k < W_PER; ++k) {
+            const bool in = (k + 1) * 256 <= W_UNITS || t + 256 * k < W_UNITS;
+            vw[k] = __builtin_amdgcn_raw_buffer_load_b128(rw_, in ? ow : 0x80000000u, 2 * c0 + k * wstep, 0);
+        }
+    };
+    auto stage = [&]() {
+#pragma unroll
+        for (int k = 0; k < IN_PER; ++k)
+            if ((k + 1) * 256 <= IN_UNITS || t + 256 * k < IN_UNITS)
+                *reinterpret_cast<u32x4*>(&Is[ldst + k * (256 / UPP) * PITCH]) = vin[k];
+#pragma unroll
+        for (int k = 0; k < W_PER; ++k)
+            if ((k + 1) * 256 <= W_UNITS || t + 256 * k < W_UNITS)
+                *reinterpret_cast<u32x4*>(&Ws[ldst + k * (256 / UPP) * PITCH]) = vw[k];
+    };
     f32x16 acc[2][NB];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
@@ -353,125 +418,111 @@ __global__ __launch_bounds__(256) void k_conv9(ConvArgs a) {
         for (int j = 0; j < NB; ++j)
 #pragma unroll
             for (int q = 0; q < 16; ++q) acc[i][j][q] = 0.0f;
-// the products of one staged chunk: nine taps x two K = 16 steps
-#define C9_PRODUCTS()                                                                                 \
-    _Pragma("unroll") for (int tap = 0; tap < 9; ++tap) {                                            \
-        const int dy = tap / 3 - 1, dx = tap % 3 - 1;                                                 \
-        _Pragma("unroll") for (int ks = 0; ks < 2; ++ks) {                                            \
-            Frag<__bf16> fa[2], fb[NB];                                                               \
-            _Pragma("unroll") for (int i = 0; i < 2; ++i) {                                           \
-                const int r = 2 * wave + i + 1 + dy, px = (l & 31) + 1 + dx;                          \
-                fa[i].v = *reinterpret_cast<const bf16x8*>(&Is[(r * IX + px) * kC9Pitch + 16 * ks + 8 * kg]); \
-            }                                                                                         \
-            _Pragma("unroll") for (int j = 0; j < NB; ++j) fb[j].v = *reinterpret_cast<const bf16x8*>( \
-                &Ws[((32 * j + (l & 31)) * 9 + tap) * kC9Pitch + 16 * ks + 8 * kg]);                  \
-            _Pragma("unroll") for (int i = 0; i < 2; ++i)                                            \
-                _Pragma("unroll") for (int j = 0; j < NB; ++j) mma(acc[i][j], fa[i], fb[j]);          \
-        }                                                                                             \
-    }
-    // PF: the next chunk's input and weights wait in registers while this
-    // chunk's products run (more registers; pays where few tiles share the
-    // chip); otherwise each chunk is loaded straight into LDS
-    if constexpr (!PF) {
-        for (int c0 = 0; c0 < a.cin; c0 += 32) {
-            for (int u = t; u < IN_UNITS; u += 256) {
-                const int cg = u & 3, px = (u >> 2) % IX, r = (u >> 2) / IX;
-                const int yy = y0 - 1 + r;
-                int xx = x0 - 1 + px;
-                xx = xx < 0 ? xx + a.W : (xx >= a.W ? xx - a.W : xx);
-                uint4 v = make_uint4(0u, 0u, 0u, 0u);
-                if (yy >= 0 && yy < a.H)
-                    v = *reinterpret_cast<const uint4*>(in + ((int64_t)(b * a.H + yy) * a.W + xx) * a.in_cs + c0 + 8 * cg);
-                *reinterpret_cast<uint4*>(&Is[(r * IX + px) * kC9Pitch + 8 * cg]) = v;
-            }
-            for (int u = t; u < W_UNITS; u += 256) {
-                const int cg = u & 3, tap = (u >> 2) % 9, n = (u >> 2) / 9;
-                *reinterpret_cast<uint4*>(&Ws[(n * 9 + tap) * kC9Pitch + 8 * cg]) =
-                    *reinterpret_cast<const uint4*>(w + (int64_t)(nbase + n) * wrow + tap * a.cin + c0 + 8 * cg);
-            }
-            __syncthreads();
-            C9_PRODUCTS()
-            __syncthreads();
-        }
-    } else {
-    constexpr int IN_PER = (IN_UNITS + 255) / 256, W_PER = (W_UNITS + 255) / 256;
-    u32x4 rin[IN_PER], rw[W_PER];
-#define C9_GLOAD(C0)                                                                                             \
-    {                                                                                                            \
-        _Pragma("unroll") for (int k = 0; k < IN_PER; ++k) {                                                       \
-            const int u = t + 256 * k;                                                                           \
-            rin[k] = u32x4{0u, 0u, 0u, 0u};                                                                 \
-            if (u < IN_UNITS) {                                                                                  \
-                const int cg = u & 3, px = (u >> 2) % IX, r = (u >> 2) / IX;                                     \
-                const int yy = y0 - 1 + r;                                                                       \
-                int xx = x0 - 1 + px;                                                                            \
-                xx = xx < 0 ? xx + a.W : (xx >= a.W ? xx - a.W : xx);                                            \
-                if (yy >= 0 && yy < a.H)                                                                         \
-                    rin[k] = *reinterpret_cast<const u32x4*>(in + ((int64_t)(b * a.H + yy) * a.W + xx) * a.in_cs + \
-                                                             (C0) + 8 * cg);                                     \
-            }                                                                                                    \
-        }                                                                                                        \
-        _Pragma("unroll") for (int k = 0; k < W_PER; ++k) {                                                        \
-            const int u = t + 256 * k;                                                                           \
-            if (u < W_UNITS) {                                                                                   \
-                const int cg = u & 3, tap = (u >> 2) % 9, n = (u >> 2) / 9;                                      \
-                rw[k] = *reinterpret_cast<const u32x4*>(w + (int64_t)(nbase + n) * wrow + tap * a.cin + (C0) + 8 * cg); \
-            }                                                                                                    \
-        }                                                                                                        \
-    }
-#define C9_LSTORE()                                                                                              \
-    {                                                                                                            \
-        _Pragma("unroll") for (int k = 0; k < IN_PER; ++k) {                                                       \
-            const int u = t + 256 * k;                                                                           \
-            if (u < IN_UNITS) {                                                                                  \
-                const int cg = u & 3, px = (u >> 2) % IX, r = (u >> 2) / IX;                                     \
-                *reinterpret_cast<u32x4*>(&Is[(r * IX + px) * kC9Pitch + 8 * cg]) = rin[k];                      \
-            }                                                                                                    \
-        }                                                                                                        \
-        _Pragma("unroll") for (int k = 0; k < W_PER; ++k) {                                                        \
-            const int u = t + 256 * k;                                                                           \
-            if (u < W_UNITS) {                                                                                   \
-                const int cg = u & 3, tap = (u >> 2) % 9, n = (u >> 2) / 9;                                      \
-                *reinterpret_cast<u32x4*>(&Ws[(n * 9 + tap) * kC9Pitch + 8 * cg]) = rw[k];                       \
-            }                                                                                                    \
-        }                                                                                                        \
-    }
-    C9_GLOAD(0)
-    C9_LSTORE()
-    __syncthreads();
-    for (int c0 = 0; c0 < a.cin; c0 += 32) {
-        if (c0 + 32 < a.cin) C9_GLOAD(c0 + 32)
-        C9_PRODUCTS()
+    load(0);
+    for (int c0 = 0; c0 < a.cin; c0 += 16 * KS) {
+        stage();
         __syncthreads();
-        if (c0 + 32 < a.cin) {
-            C9_LSTORE()
-            __syncthreads();
-        }
+        if (c0 + 16 * KS < a.cin) load(c0 + 16 * KS);
+        Frag<__bf16> fp[3][KS];                      // the second row's operand of the tap above
+#pragma unroll
+        for (int dy = 0; dy < 3; ++dy)
+#pragma unroll
+            for (int dx = 0; dx < 3; ++dx) {
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks) {
+                    const int e = 16 * ks + 8 * kg;
+                    const __bf16* at = &Is[((2 * wave + dy) * IX + (l & 31) + dx) * PITCH + e];
+                    Frag<__bf16> fa[2], fb[NB];
+                    if (dy == 0) fa[0].v = *reinterpret_cast<const bf16x8*>(at);
+                    else fa[0] = fp[dx][ks];
+                    fa[1].v = *reinterpret_cast<const bf16x8*>(at + IX * PITCH);
+                    fp[dx][ks] = fa[1];
+#pragma unroll
+                    for (int j = 0; j < NB; ++j)
+                        fb[j].v = *reinterpret_cast<const bf16x8*>(&Ws[((32 * j + (l & 31)) * 9 + 3 * dy + dx) * PITCH + e]);
+#pragma unroll
+                    for (int i = 0; i < 2; ++i)
+#pragma unroll
+                        for (int j = 0; j < NB; ++j) mma(acc[i][j], fb[j], fa[i]);
+                }
+            }
+        __syncthreads();
     }
-#undef C9_GLOAD
-#undef C9_LSTORE
-    }
-#undef C9_PRODUCTS
+    // lane l holds pixel l % 32 of both rows, channels acc_row(q, l)
     const __bf16* mask = static_cast<const __bf16*>(a.mask);
+    const int64_t p0 = (int64_t)(b * a.H + y0 + 2 * wave) * a.W + x0;  // first pixel of the wave's rows
+    if (a.vec) {
+        // 16-byte units of the wave's 64 pixels: unit u is channels 8 (u % (4 NB)) of pixel u / (4 NB)
+        u32x4 mk[4 * NB];
+        const int cg = 8 * (l % (4 * NB));
+        auto pixel = [&](int k) {
+            const int px = (l + 64 * k) / (4 * NB);
+            return p0 + (px >> 5) * a.W + (px & 31);
+        };
 #pragma unroll
-    for (int j = 0; j < NB; ++j) {
-        const int n = nbase + 32 * j + (l & 31);
-        if (n >= a.cout) continue;
-        const float bv = a.bias ? a.bias[n] : 0.0f;
+        for (int k = 0; k < 4 * NB; ++k) mk[k] = u32x4{0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};
+        if (mask) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+            for (int k = 0; k < 4 * NB; ++k)
+                mk[k] = *reinterpret_cast<const u32x4*>(mask + pixel(k) * a.mask_cs + a.mask_co + nbase + cg);
+        }
+        float bv[NB][16];
 #pragma unroll
-            for (int q = 0; q < 16; ++q) {
-                const int p = (b * a.H + y0 + 2 * wave + i) * a.W + x0 + acc_row(q, l);
+        for (int j = 0; j < NB; ++j)
+#pragma unroll
+            for (int q = 0; q < 16; ++q) bv[j][q] = 0.0f;
+        if (a.bias) {
+#pragma unroll
+            for (int j = 0; j < NB; ++j)
+#pragma unroll
+                for (int q = 0; q < 16; ++q) bv[j][q] = a.bias[nbase + 32 * j + acc_row(q, l)];
+        }
+        __bf16* const Os = lds + wave * 64 * kOutPitch;
+#pragma unroll
+        for (int j = 0; j < NB; ++j)
+#pragma unroll
+            for (int g = 0; g < 4; ++g)
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    bf16x4 o;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const float v = acc[i][j][4 * g + e] + bv[j][4 * g + e];
+                        o[e] = (__bf16)(v > 0.0f || !a.relu ? v : 0.0f);
+                    }
+                    *reinterpret_cast<bf16x4*>(&Os[(32 * i + (l & 31)) * kOutPitch + 32 * j + 8 * g + 4 * kg]) = o;
+                }
+        __syncthreads();
+        __bf16* const out = static_cast<__bf16*>(a.out) + a.out_co + nbase + cg;
+#pragma unroll
+        for (int k = 0; k < 4 * NB; ++k) {
+            bf16x8 o = *reinterpret_cast<const bf16x8*>(&Os[(l + 64 * k) / (4 * NB) * kOutPitch + cg]);
+            const bf16x8 m = __builtin_bit_cast(bf16x8, mk[k]);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) o[e] = (float)m[e] > 0.0f ? o[e] : (__bf16)0.0f;
+            *reinterpret_cast<bf16x8*>(out + pixel(k) * a.out_cs) = o;
+        }
+        return;
+    }
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+            const int n = nbase + 32 * j + acc_row(q, l);
+            if (n >= a.cout) continue;
+            const float bv = a.bias ? a.bias[n] : 0.0f;
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const int64_t p = p0 + i * a.W + (l & 31);
                 float v = acc[i][j][q] + bv;
                 if (a.relu) v = v > 0.0f ? v : 0.0f;
-                if (mask && !(to_f(mask[(int64_t)p * a.mask_cs + a.mask_co + n]) > 0.0f)) v = 0.0f;
+                if (mask && !(to_f(mask[p * a.mask_cs + a.mask_co + n]) > 0.0f)) v = 0.0f;
                 if (a.out_f32)
-                    static_cast<float*>(a.out)[(int64_t)p * a.out_cs + a.out_co + n] = v;
+                    static_cast<float*>(a.out)[p * a.out_cs + a.out_co + n] = v;
                 else
-                    static_cast<__bf16*>(a.out)[(int64_t)p * a.out_cs + a.out_co + n] = (__bf16)v;
+                    static_cast<__bf16*>(a.out)[p * a.out_cs + a.out_co + n] = (__bf16)v;
             }
-    }
+        }
 }
 
 // ------------------------------------------------------------------ weight gradient

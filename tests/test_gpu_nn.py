@@ -373,3 +373,47 @@ def test_layer_forward_exact_small(torch_mod, lbm_mod):
     """32 x 64 lattice: too few tiles for the tap-holding kernel, every layer
     on the LDS-tiled GEMM."""
     _layer_forward_case(torch_mod, lbm_mod, H, W, 2, 82)
+
+
+@pytest.mark.parametrize("ch,h,w,b", [
+    # full size: nine-tap tiles of one block of output channels on 16, 32 and 96
+    # (three chunks) input channels; half size: staged tiles on 32, 64 and 128
+    ((32, 64, 64, 128), 64, 128, 8),
+    # nine-tap tiles of two blocks of output channels on 64 and 96 channels
+    ((64, 32, 32, 32), 64, 128, 16),
+])
+def test_convolution_tiles_bf16(torch_mod, lbm_mod, ch, h, w, b):
+    """Lattices and batches large enough for the tiled convolutions (whole
+    tiles at both walls and across the periodic side), against the oracle with
+    the same bfloat16 storage: the module's BF16 bar per tensor."""
+    torch = torch_mod
+    rng = np.random.default_rng(31)
+    layers = []
+    for ci, o, _ in co.layer_shapes(ch):
+        layers.append((rng.normal(size=(o, 3, 3, ci)) * np.sqrt(2.0 / (9 * ci)), rng.normal(size=o) * 0.05))
+    p = co.pack(layers)
+    yy, xx = np.mgrid[0:h, 0:w]
+    x = np.zeros((b, h, w, 2))
+    for k in range(b):
+        cx, cy, r = rng.uniform(0, w), rng.uniform(8, h - 8), rng.uniform(3, 12)
+        dx = (xx - cx + w / 2) % w - w / 2
+        x[k, :, :, 0] = dx ** 2 + (yy - cy) ** 2 <= r * r
+        x[k, :, :, 1] = rng.uniform(0.01, 1.0)
+    _say(f"tiles {ch} {h}x{w} batch {b}: oracle")
+    y_ref, tape = co.forward(p, x, ch, q=co.bf16)
+    _, gy = co.masked_mse(y_ref, 0.5 * np.tanh(y_ref) + 0.1, x[..., 0] == 0)
+    g_ref = co.backward(p, tape, gy, ch, q=co.bf16)
+    _say("GPU")
+    net = lbm_mod.WarmStartNet(h, w, b, dtype="bf16", ch=ch)
+    net.set_params(torch.from_numpy(p))
+    y = net.forward(torch.from_numpy(x)).cpu().numpy()
+    net.backward(torch.from_numpy(gy))
+    g = net.grads().cpu().numpy()
+    assert rel_l2(y, y_ref) <= 2e-2
+    k = 0
+    for n, (ci, o, _) in enumerate(co.layer_shapes(ch)):
+        for size, name in ((o * 9 * ci, "w"), (o, "b")):
+            e = rel_l2(g[k:k + size], g_ref[k:k + size])
+            _say(f"layer {n} {name} gradient rel err {e:.3e}")
+            assert e <= 2e-2, (n, name)
+            k += size
