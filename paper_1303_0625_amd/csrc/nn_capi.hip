@@ -310,7 +310,18 @@ void conv(lbm_nn* n, int level, const void* in, int in_cs, int cin, const void* 
             case 0: CONV_LDS_LAUNCH(2, 2, 2, 2) break;
             case 1: CONV_LDS_LAUNCH(2, 2, 2, 1) break;
             case 2: CONV_LDS_LAUNCH(4, 1, 2, 1) break;
-            case 3: CONV_LDS_LAUNCH(2, 2, 1, 1) break;
+            case 3:
+                // (the small tile's stages are bound by their loads' latency:
+                // the widest stage that divides the channels, in the same order
+                // of the sum)
+                if (cin % 128 == 0)
+                    k_conv_lds<2, 2, 1, 1, 128><<<g, 256, 0, n->st>>>(a);
+                else if (cin % 64 == 0)
+                    k_conv_lds<2, 2, 1, 1, 64><<<g, 256, 0, n->st>>>(a);
+                else {
+                    CONV_LDS_LAUNCH(2, 2, 1, 1)
+                }
+                break;
             default: CONV_LDS_LAUNCH(4, 1, 1, 1) break;
         }
 #undef CONV_LDS_LAUNCH

@@ -184,11 +184,16 @@ __global__ __launch_bounds__(kConvWaves * 64) void k_conv(ConvArgs a) {
 }
 
 // One 16-byte A segment of the BF16 convolution: 8 channels from c of node
-// (b, yy, xx) with x periodic, zero outside the walls or for b < 0.
-__device__ __forceinline__ uint4 conv_load_a(const __bf16* in, int b, int yy, int xx, int H, int W, int cs, int c) {
+// (b, yy, xx) with x periodic; ok is cleared outside the walls and for b < 0,
+// where the first node is read instead (no branch around a load: the loads of
+// a stage are in flight together).
+__device__ __forceinline__ u32x4 conv_load_a(const __bf16* in, int b, int yy, int xx, int H, int W, int cs, int c,
+                                             bool& ok) {
     xx = xx < 0 ? xx + W : (xx >= W ? xx - W : xx);
-    if (b >= 0 && yy >= 0 && yy < H) return *reinterpret_cast<const uint4*>(in + ((int64_t)(b * H + yy) * W + xx) * cs + c);
-    return make_uint4(0, 0, 0, 0);
+    ok = b >= 0 && yy >= 0 && yy < H;
+    const int q = (b * H + yy) * W + xx;
+    const int64_t p = ok ? q : 0;
+    return *reinterpret_cast<const u32x4*>(in + p * cs + c);
 }
 
 // BF16 convolution with LDS-staged operands.  Workgroup tile: BM = 32 WM MW
@@ -198,7 +203,10 @@ __device__ __forceinline__ uint4 conv_load_a(const __bf16* in, int b, int yy, in
 // outside the walls) and B tile (BN weight rows) are read from global memory
 // into registers while the MFMAs of the previous stage run from LDS, then
 // written to the other of two LDS buffers (rows padded by 8 elements), with
-// one barrier per stage.  Same arguments and epilogue as k_conv.
+// one barrier per stage.  Same arguments and epilogue as k_conv.  Bound by the
+// latency of a stage's loads: they carry no branch, and the smallest tile takes
+// stages of up to 128 channels (256 -> 256 channels at 32x16, batch 8: 38 us
+// with stages of 32, 21 us).
 template <int MW, int NW, int WM, int WN, int BK>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 3))) void k_conv_lds(ConvArgs a) {
     static_assert(MW * NW == 4, "four waves");
@@ -235,13 +243,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 3))) voi
 #pragma unroll
     for (int r = 0; r < B_PER; ++r) {
         const int id = t + 256 * r;
-        br[r] = id < B_SEGS ? id / SEG : -1;
+        br[r] = id < B_SEGS ? id / SEG : 0;  // (a thread without a unit reads row 0 and stores nothing)
         bsg[r] = id % SEG;
     }
     const int kchunks = a.cin / BK;
     const int nst = 9 * kchunks;
     const int wrow = 9 * a.cin;
-    uint4 ra[A_PER], rb[B_PER];
+    u32x4 ra[A_PER], rb[B_PER];
+    bool oka[A_PER];
     f32x16 acc[WM][WN];
 #pragma unroll
     for (int i = 0; i < WM; ++i)
@@ -254,16 +263,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 3))) voi
         const int tap_ = (ST) / kchunks, c0_ = ((ST) - tap_ * kchunks) * BK;                                    \
         const int dy_ = tap_ / 3 - 1, dx_ = tap_ % 3 - 1;                                                      \
         _Pragma("unroll") for (int r = 0; r < A_PER; ++r) ra[r] =                                                \
-            conv_load_a(in, ab[r], ay[r] + dy_, ax[r] + dx_, a.H, a.W, a.in_cs, c0_ + 8 * as_[r]);              \
-        _Pragma("unroll") for (int r = 0; r < B_PER; ++r) if (br[r] >= 0) rb[r] =                                \
-            *reinterpret_cast<const uint4*>(w + (int64_t)(nbase + br[r]) * wrow + tap_ * a.cin + c0_ + 8 * bsg[r]); \
+            conv_load_a(in, ab[r], ay[r] + dy_, ax[r] + dx_, a.H, a.W, a.in_cs, c0_ + 8 * as_[r], oka[r]);      \
+        _Pragma("unroll") for (int r = 0; r < B_PER; ++r) rb[r] = *reinterpret_cast<const u32x4*>(              \
+            w + (int64_t)(nbase + br[r]) * wrow + tap_ * a.cin + c0_ + 8 * bsg[r]);                             \
     }
 #define CONV_LDS_LSTORE(BUF)                                                                                   \
     {                                                                                                          \
-        _Pragma("unroll") for (int r = 0; r < A_PER; ++r) if (t + 256 * r < A_SEGS)                              \
-            *reinterpret_cast<uint4*>(&As[BUF][ar[r] * LDK + 8 * as_[r]]) = ra[r];                              \
-        _Pragma("unroll") for (int r = 0; r < B_PER; ++r) if (br[r] >= 0)                                        \
-            *reinterpret_cast<uint4*>(&Bs[BUF][br[r] * LDK + 8 * bsg[r]]) = rb[r];                              \
+        _Pragma("unroll") for (int r = 0; r < A_PER; ++r) if ((r + 1) * 256 <= A_SEGS || t + 256 * r < A_SEGS)   \
+            *reinterpret_cast<u32x4*>(&As[BUF][ar[r] * LDK + 8 * as_[r]]) = oka[r] ? ra[r] : u32x4{0u, 0u, 0u, 0u}; \
+        _Pragma("unroll") for (int r = 0; r < B_PER; ++r) if ((r + 1) * 256 <= B_SEGS || t + 256 * r < B_SEGS)   \
+            *reinterpret_cast<u32x4*>(&Bs[BUF][br[r] * LDK + 8 * bsg[r]]) = rb[r];                              \
     }
     CONV_LDS_GLOAD(0)
     CONV_LDS_LSTORE(0)
@@ -668,8 +677,13 @@ __global__ __launch_bounds__(256) void k_wgrad(WgradArgs a) {
 // operands are the dx = 0 vector shifted by one pixel, with the neighbouring
 // pixel taken from the words before and after it, so the g operand and the
 // x vector are read once for three products.  Tiles [split * tps, + tps)
-// go through a double-buffered LDS stage (next tile's global loads in
-// registers during the products).  Partial sums go to part[split] as for
+// go through a double-buffered LDS stage.  Bound by latency and by the staging
+// (one barrier per tile, few workgroups on a unit, packing and LDS writes about
+// a third of the time each): the global loads of the next three or four tiles
+// are in flight, waited for by their number, and the staged rows are laid so
+// that their writes spread over the banks.  256x128, batch 8, us before (one
+// tile ahead, waited for whole) and now: 32 x 32 channels 33, 25; 96 x 32 69, 57;
+// 640 x 128 at quarter size 81, 65.  Partial sums go to part[split] as for
 // k_wgrad; the first input block of a split also sums g into the bias slot,
 // per channel group in pixel order, then over the groups in order.
 constexpr int kWgTile = 32;                // pixels per tile
@@ -698,11 +712,14 @@ __device__ inline uint32_t shift1(uint32_t a, uint32_t b) { return (a >> 16) | (
 template <int MB, int NB>
 __global__ __launch_bounds__(192 * NB) void k_wgrad9(Wgrad9Args a) {
     constexpr int NT = 192 * NB;
+    constexpr int D = MB == 2 ? 3 : 4;           // tiles in flight
     constexpr int NG = (kWgTile / 4) * 4 * MB;   // g units: 4 pixels x 8 channels
     constexpr int NX = 3 * kWgGroups * 4 * NB;   // x units
     static_assert(NG + NX <= NT, "one staging unit per thread");
-    __shared__ __align__(16) __bf16 Xs[2][3][32 * NB][kWgXPitch];
-    __shared__ __align__(16) __bf16 Gs[2][32 * MB][kWgGPitch];
+    // rows of 8 channels, then 16 bytes: without them the staging writes of
+    // neighbouring channel groups met in two banks
+    __shared__ __align__(16) __bf16 Xs[2][3][4 * NB][8 * kWgXPitch + 8];
+    __shared__ __align__(16) __bf16 Gs[2][4 * MB][8 * kWgGPitch + 8];
     __shared__ float bred[kWgTile / 4][32 * MB];
     const int t = threadIdx.x;
     const int l = t & 63;
@@ -735,38 +752,42 @@ __global__ __launch_bounds__(192 * NB) void k_wgrad9(Wgrad9Args a) {
     float bsum[8];
 #pragma unroll
     for (int c = 0; c < 8; ++c) bsum[c] = 0.0f;
-    uint4 reg[4];
+    // tile s + D's units are loaded while tile s's products run
+    uint4 reg[D][4];
+    uint32_t real[D];  // all bits: reg[s] holds pixels of the image
+    const __bf16* const src = x_ok ? a.x + xch : (is_g ? a.g + gch : a.g);
+    const int64_t cs = x_ok ? a.x_cs : a.g_cs;
 
-    auto gload = [&](int tile) {
+    // (one path for all threads: a unit without pixels reads the first ones and
+    // stores zeros, so that the loads of the tiles between are waited for by
+    // their number)
+    auto gload = [&](int tile, int s) {
         const int seg = tile % nseg;
         const int row = tile / nseg;  // b * H + y
         const int x0 = seg * kWgTile;
+        const int yy = row % a.H + (is_x ? u_row - 1 : 0);
+        int xx = x0 + 4 * u_grp - (is_x ? 4 : 0);
+        xx = xx < 0 ? xx + a.W : (xx >= a.W ? xx - a.W : xx);
+        const bool ok = (is_g || x_ok) && yy >= 0 && yy < a.H;
+        const int q = (row + (is_x ? u_row - 1 : 0)) * a.W + xx;
+        const int64_t p = ok ? q : 0;
+        real[s] = ok ? 0xffffffffu : 0u;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) reg[e] = make_uint4(0u, 0u, 0u, 0u);
-        if (is_g) {
-            const int64_t p = (int64_t)row * a.W + x0 + 4 * u_grp;
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                reg[e] = *reinterpret_cast<const uint4*>(a.g + (p + e) * a.g_cs + gch);
-        } else if (x_ok) {
-            const int b = row / a.H;
-            const int yy = row - b * a.H + u_row - 1;
-            if (yy >= 0 && yy < a.H) {
-                int xx = x0 - 4 + 4 * u_grp;
-                xx = xx < 0 ? xx + a.W : (xx >= a.W ? xx - a.W : xx);
-                const int64_t p = ((int64_t)b * a.H + yy) * a.W + xx;
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    reg[e] = *reinterpret_cast<const uint4*>(a.x + (p + e) * a.x_cs + xch);
-            }
-        }
+        for (int e = 0; e < 4; ++e) reg[s][e] = *reinterpret_cast<const uint4*>(src + (p + e) * cs);
     };
-    auto lstore = [&](int buf) {
+    auto lstore = [&](int buf, int s) {
         if (!is_g && !is_x) return;
-        const uint32_t w[4][4] = {{reg[0].x, reg[0].y, reg[0].z, reg[0].w},
-                                  {reg[1].x, reg[1].y, reg[1].z, reg[1].w},
-                                  {reg[2].x, reg[2].y, reg[2].z, reg[2].w},
-                                  {reg[3].x, reg[3].y, reg[3].z, reg[3].w}};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            reg[s][e].x &= real[s];
+            reg[s][e].y &= real[s];
+            reg[s][e].z &= real[s];
+            reg[s][e].w &= real[s];
+        }
+        const uint32_t w[4][4] = {{reg[s][0].x, reg[s][0].y, reg[s][0].z, reg[s][0].w},
+                                  {reg[s][1].x, reg[s][1].y, reg[s][1].z, reg[s][1].w},
+                                  {reg[s][2].x, reg[s][2].y, reg[s][2].z, reg[s][2].w},
+                                  {reg[s][3].x, reg[s][3].y, reg[s][3].z, reg[s][3].w}};
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             // channels 2k and 2k + 1 of the four pixels
@@ -775,21 +796,21 @@ __global__ __launch_bounds__(192 * NB) void k_wgrad9(Wgrad9Args a) {
             __bf16* d0;
             __bf16* d1;
             if (is_g) {
-                d0 = &Gs[buf][8 * u_ch + 2 * k][4 * u_grp];
-                d1 = &Gs[buf][8 * u_ch + 2 * k + 1][4 * u_grp];
+                d0 = &Gs[buf][u_ch][2 * k * kWgGPitch + 4 * u_grp];
+                d1 = d0 + kWgGPitch;
             } else {
-                d0 = &Xs[buf][u_row][8 * u_ch + 2 * k][4 + 4 * u_grp];
-                d1 = &Xs[buf][u_row][8 * u_ch + 2 * k + 1][4 + 4 * u_grp];
+                d0 = &Xs[buf][u_row][u_ch][2 * k * kWgXPitch + 4 + 4 * u_grp];
+                d1 = d0 + kWgXPitch;
             }
             *reinterpret_cast<uint2*>(d0) = ev;
             *reinterpret_cast<uint2*>(d1) = od;
         }
     };
-    auto bias_add = [&]() {
+    auto bias_add = [&](int s) {
         if (!(bias_wg && is_g)) return;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            const uint32_t w[4] = {reg[e].x, reg[e].y, reg[e].z, reg[e].w};
+            const uint32_t w[4] = {reg[s][e].x, reg[s][e].y, reg[s][e].z, reg[s][e].w};
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 bsum[2 * k] += __uint_as_float(w[k] << 16);
@@ -806,17 +827,20 @@ __global__ __launch_bounds__(192 * NB) void k_wgrad9(Wgrad9Args a) {
 #pragma unroll
             for (int q = 0; q < 16; ++q) acc[i][d][q] = 0.0f;
 
-    gload(t0);
-    bias_add();
-    lstore(0);
-    __syncthreads();
-    for (int tile = t0; tile < t1; ++tile) {
-        const int buf = (tile - t0) & 1;
-        if (tile + 1 < t1) gload(tile + 1);
+#pragma unroll
+    for (int s = 0; s < D; ++s) gload(min(t0 + s, t1 - 1), s);
+    int buf = 0;
+    auto step = [&](int tile, int s, bool more) {
+        // (the other buffer's readers are through when all have passed this
+        // tile's barrier, before it is written again)
+        bias_add(s);
+        lstore(buf, s);
+        __syncthreads();
+        if (more) gload(min(tile + D, t1 - 1), s);
 #pragma unroll
         for (int ks = 0; ks < kWgTile / 16; ++ks) {
             const int k8 = 16 * ks + 8 * (l >> 5);
-            const __bf16* xr = &Xs[buf][wr][32 * wj + (l & 31)][8 + k8];
+            const __bf16* xr = &Xs[buf][wr][4 * wj + (l >> 3 & 3)][(l & 7) * kWgXPitch + 8 + k8];
             const uint4 mid = *reinterpret_cast<const uint4*>(xr);
             const uint32_t prev = *reinterpret_cast<const uint32_t*>(xr - 2);
             const uint32_t next = *reinterpret_cast<const uint32_t*>(xr + 8);
@@ -832,17 +856,21 @@ __global__ __launch_bounds__(192 * NB) void k_wgrad9(Wgrad9Args a) {
 #pragma unroll
             for (int i = 0; i < MB; ++i) {
                 Frag<__bf16> fa;
-                fa.v = *reinterpret_cast<const bf16x8*>(&Gs[buf][32 * i + (l & 31)][k8]);
+                fa.v = *reinterpret_cast<const bf16x8*>(&Gs[buf][4 * i + (l >> 3 & 3)][(l & 7) * kWgGPitch + k8]);
 #pragma unroll
                 for (int d = 0; d < 3; ++d) mma(acc[i][d], fa, fb[d]);
             }
         }
-        if (tile + 1 < t1) {
-            bias_add();
-            lstore(buf ^ 1);
-        }
-        __syncthreads();
+        buf ^= 1;
+    };
+    int base = t0;
+    for (; base + D <= t1; base += D) {
+#pragma unroll
+        for (int s = 0; s < D; ++s) step(base + s, s, true);
     }
+#pragma unroll
+    for (int s = 0; s < D - 1; ++s)
+        if (base + s < t1) step(base + s, s, false);
 
     const int64_t nw = (int64_t)a.cout * 9 * a.cin;
     float* part = a.part + (int64_t)split * (nw + a.cout);
