@@ -556,14 +556,18 @@ void backward_t(lbm_nn* n) {
 template <typename T>
 void pack_weights_t(lbm_nn* n) {
     const Plan& p = n->p;
+    static_assert(kLayers <= kMaxLayers, "layers of one launch");
+    PackArgs pa = {};
     for (int k = 0; k < kLayers; ++k) {
         const LayerDev& L = p.L[k];
         const int64_t m = std::max<int64_t>(std::max<int64_t>((int64_t)L.cout_pad * 9 * L.cin_pad,
                                                              (int64_t)L.cin_dg * 9 * L.cout_pad),
                                             L.cout_pad);
-        k_pack_weights<T><<<blocks(m), kEw, 0, n->st>>>(at<float>(n, p.o_master), L, at<T>(n, p.o_wf),
-                                                       at<T>(n, p.o_wt), at<float>(n, p.o_bias));
+        pa.L[k] = L;
+        pa.first[k + 1] = pa.first[k] + (int)blocks(m);
     }
+    k_pack_weights<T><<<pa.first[kLayers], kEw, 0, n->st>>>(at<float>(n, p.o_master), pa, at<T>(n, p.o_wf),
+                                                           at<T>(n, p.o_wt), at<float>(n, p.o_bias));
 }
 
 void pack_weights(lbm_nn* n) {
