@@ -259,7 +259,8 @@ lbm_status lbm_checkpoint_bytes(const lbm_ctx* ctx, size_t* bytes);
 lbm_status lbm_save(lbm_ctx* ctx, void* d_dst, size_t bytes);
 lbm_status lbm_load(lbm_ctx* ctx, const void* d_src, size_t bytes);
 
-/* Kernel timing (instrumentation).  While enabled, every time-step launch
+/* Kernel timing (instrumentation).  While enabled, lattices that take two
+ * steps per launch take one, and every time-step launch
  * (one kernel per step: force, moving-body and fused advection + bounce-back
  * + collision workgroups, the last moving 18 populations per fluid node) is
  * timed by a pair of HIP events attached to its dispatch on the context's

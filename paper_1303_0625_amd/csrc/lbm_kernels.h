@@ -2,10 +2,11 @@
 //
 // State convention: the workspace holds the post-collision deviations
 // d~_i(x, t) = f~_i(x, t) - w_i rho0 of every fluid node of geometry G_t, SoA
-// [9][ny][pitch], in two ping-pong buffers selected by the parity of t.  One
-// time step t -> t+1 is one launch of k_fused whose workgroups take one of
-// three roles; the roles read only step-t data and write disjoint outputs,
-// so they run concurrently:
+// [9][ny][pitch], in two ping-pong buffers that change with every launch.  One
+// time step t -> t+1 is one launch of k_fused (large lattices of fixed geometry:
+// two steps are one launch of k_pair) whose workgroups take one of three roles;
+// the roles read only step-t data and write disjoint outputs, so they run
+// concurrently:
 //   force      Eqs. 4-7 on the link lists of G_t (reads f~(t)), chunked over
 //              workgroups, with a fixed-order final sum per solid
 //   move       per translating body: owner map of G_{t+1} in its swept box,
