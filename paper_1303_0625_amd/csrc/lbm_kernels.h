@@ -963,6 +963,8 @@ constexpr uint8_t kWallMark = 255;
 constexpr int kMoverGap = 8;
 constexpr int kNewbornBatch = 4;   // newborn nodes refilled together
 constexpr int kNewbornMax = 128;   // newborn nodes of one body in one step
+// Groups of 64 box nodes: two byte maps of the box fit the 160 KiB of LDS.
+constexpr int kBoxGroups = 160 * 1024 / 2 / 64;
 
 struct MoveArgs {
     int nx, ny, opitch, walls;
@@ -1010,7 +1012,12 @@ struct MoveShared {
     int nb_count;  // newborn nodes (part 1), links (part 0)
     int nb_list[kNewbornMax];
     int8_t nb_use[kNewbornBatch][8];  // -1: no participation, else 0/1/2
-    C nb_val[kNewbornBatch][8][3][9];  // (part 0: link counts per 64 box nodes)
+    // (part 0: links per 64 box nodes, 16 bits each, over the same bytes)
+    union {
+        C nb_val[kNewbornBatch][8][3][9];
+        uint16_t group[kBoxGroups];
+    };
+    static_assert(sizeof(group) <= sizeof(nb_val), "the largest box's groups take no more LDS than the refill");
     C nb_new[kNewbornBatch][9];
     C nb_mom[kNewbornBatch][4];
 };
@@ -1187,9 +1194,11 @@ __device__ inline void move_role(int m, uint8_t* __restrict__ lds, MoveShared<T>
     // links in the groups before, plus that of the lanes before in its own
     // (the ballots of the eight bits).  No thread walks a run of nodes: with a
     // contiguous run per thread this phase took 10 to 16 us of the mover's 13
-    // to 23 (discs of r = 9 to 15), now 4 to 5.
+    // to 23 (discs of r = 9 to 15), now 4 to 5.  A count of links fits 16 bits:
+    // a node beside a convex body has at most three links into one of its sides,
+    // so the longest body whose box fits (a bar of 1 x 7,400 nodes) has 45,000.
     if (part == 0) {
-        int* gtot = reinterpret_cast<int*>(&sm.nb_val[0][0][0][0]);  // links per group, then before it
+        uint16_t* gtot = sm.group;  // links per group, then before it
         const int lane = (int)threadIdx.x & 63;
         const int ngrp = (N + 63) / 64;
         {
@@ -1209,21 +1218,21 @@ __device__ inline void move_role(int m, uint8_t* __restrict__ lds, MoveShared<T>
                 int c = 0;
 #pragma unroll
                 for (int i = 0; i < 8; ++i) c += __builtin_popcountll(__ballot((bits >> i & 1u) != 0u));
-                if (lane == 0) gtot[q >> 6] = c;
+                if (lane == 0) gtot[q >> 6] = (uint16_t)c;
             }
         }
         __syncthreads();
         if (threadIdx.x < 64) {
             int carry = 0;
             for (int g0 = 0; g0 < ngrp; g0 += 64) {
-                const int v = g0 + lane < ngrp ? gtot[g0 + lane] : 0;
+                const int v = g0 + lane < ngrp ? (int)gtot[g0 + lane] : 0;
                 int x = v;
 #pragma unroll
                 for (int off = 1; off < 64; off <<= 1) {
                     const int y = __shfl_up(x, off, 64);
                     if (lane >= off) x += y;
                 }
-                if (g0 + lane < ngrp) gtot[g0 + lane] = carry + x - v;
+                if (g0 + lane < ngrp) gtot[g0 + lane] = (uint16_t)(carry + x - v);
                 carry += __shfl(x, 63, 64);
             }
             if (lane == 0) sm.nb_count = carry;

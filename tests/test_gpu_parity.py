@@ -617,3 +617,35 @@ def test_two_steps_per_launch_equal_single_steps(lbm_mod, dtype, mrt, walls):
         assert bool((r.force_history(r.t - 2, 2) == b.force_history(b.t - 2, 2)).all())
         del a, b, r
         torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
+@pytest.mark.parametrize("nx,ny,body", [
+    (300, 290, lc.disc(150.4, 141.3, 120.0, vx=0.04, vy=-0.03, moves=True)),  # box of 1,016 groups of 64 nodes
+    (3640, 40, lc.box(1815.8, 19.6, 1800.0, 2.5, vx=0.05, moves=True))])      # 1,130 groups, 7,000 links
+def test_large_mover_link_lists(oracle_mod, lbm_mod, dtype, nx, ny, body):
+    """Link lists of a translating body whose box nearly fills the LDS: the
+    same links as the oracle's after every step, and force totals within the
+    storage type's rounding.  Tolerance: a stored population is off by at most
+    2 eps of its value per step, so a total by that share of the sum of its
+    terms' magnitudes, per step taken."""
+    c = lc.make_case(nx, ny, 0.8, walls_y=False, bodies=[body], name="large_mover")
+    lat = lbm_mod.Lattice(c, dtype=dtype, history_steps=16)
+    osim = oracle_sim(oracle_mod, c)
+    eps = {"f16": 2.0 ** -11, "bf16": 2.0 ** -8, "f32": 2.0 ** -24}[dtype]
+    steps = 7
+    for k in range(steps):
+        _say(f"large mover {nx}x{ny} {dtype} step {k}")
+        rec = lat.link_forces().cpu().numpy()
+        lat.step(1)
+        osim.step(1)  # its records are those of the state before
+        orec = osim.links()
+        order = [np.lexsort((r[:, 2], r[:, 0], r[:, 1])) for r in (rec, orec)]
+        assert rec.shape == orec.shape, (k, rec.shape, orec.shape)
+        np.testing.assert_array_equal(rec[order[0]][:, :4], orec[order[1]][:, :4])
+    lat.check()
+    load = link_load(osim, 1)[1]
+    h, oh = lat.force_history().cpu().numpy(), oracle_history(osim, 1)
+    err = np.abs(h[:, 1, [0, 1, 3, 4]] - oh[:, 1, [0, 1, 3, 4]]).max()
+    _say(f"force err {err:.3e}, load {load:.3e}, bound {2 * eps * steps * load:.3e}")
+    assert err <= 2 * eps * steps * load
