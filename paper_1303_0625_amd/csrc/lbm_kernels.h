@@ -1134,8 +1134,12 @@ __device__ inline void move_role(int m, uint8_t* __restrict__ lds, MoveShared<T>
     // 1. stage the owner maps (part 0 needs only the second one; the loads of a
     // round are issued before any is used, so addresses outside the walls are
     // clamped and the value replaced) and rasterise G_{t+1} on the way: the
-    // body at t+1, and what it left cleared.  Collect the newborn nodes (solid
-    // at t, fluid at t+1); their order in the list does not affect any value
+    // body at t+1, and what it left cleared.  Owners change only in the body's
+    // own range, inside the margin, and only there are they stored: where the box
+    // is wider than the lattice a node may appear again in the margin, staged
+    // after its new owner was stored, and would be cleared.  Collect the newborn
+    // nodes (solid at t, fluid at t+1); their order in the list does not affect any
+    // value
     __syncthreads();
     {
         constexpr int R = 4;
@@ -1173,7 +1177,8 @@ __device__ inline void move_role(int m, uint8_t* __restrict__ lds, MoveShared<T>
                     const uint8_t nv = wall ? v : (in ? (uint8_t)s : (v == s ? (uint8_t)0 : v));
                     on[q] = nv;
                     if (part == 0) {
-                        if (nv != v) own_n[o[r]] = nv;
+                        if (nv != v && qx >= kBoxMargin && qx < W - kBoxMargin && qy >= kBoxMargin && qy < H - kBoxMargin)
+                            own_n[o[r]] = nv;
                     } else {
                         ot[q] = ov;
                         if (ov == s && nv == 0) {

@@ -649,3 +649,20 @@ def test_large_mover_link_lists(oracle_mod, lbm_mod, dtype, nx, ny, body):
     err = np.abs(h[:, 1, [0, 1, 3, 4]] - oh[:, 1, [0, 1, 3, 4]]).max()
     _say(f"force err {err:.3e}, load {load:.3e}, bound {2 * eps * steps * load:.3e}")
     assert err <= 2 * eps * steps * load
+
+
+@pytest.mark.parametrize("vx,cx", [(-0.28125, 6.75), (0.28125, 5.25)])
+def test_mover_box_repeats_body_columns(oracle_mod, lbm_mod, vx, cx):
+    """A body whose box repeats, in its margin, a column that enters the body
+    (13 columns, box of 19 and 20, the body's edge on a node at steps 9 and
+    16): its owners are those of the oracle after every step."""
+    c = lc.make_case(13, 20, 0.8, walls_y=True, gx=1e-5, u0=(vx, 0.0), wall_v=(0.95 * vx, 0.0),
+                     bodies=[lc.box(cx, 9.4, 3.25, 2.0, vx=vx, moves=True)], name="box_repeats")
+    lat = lbm_mod.Lattice(c, dtype="f64", history_steps=64)
+    osim = oracle_sim(oracle_mod, c)
+    for _ in range(40):
+        lat.step(1)
+        osim.step(1)
+        assert (lat.fields("f64")[3].cpu().numpy() == osim.fields()[3]).all(), lat.t
+    compare_fields(lat, osim, 1e-12)
+    compare_forces(lat, osim, c, 1e-10)
