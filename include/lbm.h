@@ -306,7 +306,10 @@ typedef struct lbm_batch lbm_batch; /* opaque; lbm_batch_create / lbm_batch_dest
 
 /* Workspace bytes of a batch.  grids[n_cases] and taus[n_cases] describe the
  * cases (one dtype for all); solids holds the bodies of case 0, then of case
- * 1, ..., n_solids[c] of them for case c; no body may move. */
+ * 1, ..., n_solids[c] of them for case c; no body may move.  Batches that take
+ * two steps per launch need one more byte per (padded) node and a tile table
+ * for it, which the result includes; lbm_batch_create also takes a buffer
+ * without these, and then advances one step per launch. */
 lbm_status lbm_batch_workspace_bytes(const lbm_grid* grids, const double* taus, const lbm_solid* solids,
                                      const int32_t* n_solids, int32_t n_cases, size_t* bytes);
 

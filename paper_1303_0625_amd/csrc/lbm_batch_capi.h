@@ -66,6 +66,7 @@ lbm_status bfail(lbm_batch* b, hipError_t e, const char* what) {
     } while (0)
 
 struct BatchLayout {
+    size_t base;   // bytes without the tables of the two-step update
     size_t total;
     std::vector<CaseDev> cd;
     std::vector<BatchChunk> chunks;
@@ -211,6 +212,7 @@ const char* batch_layout(const lbm_grid* grids, const double* taus, const lbm_so
     take(B.o_tcount, 4 * (size_t)n);
     take(B.o_list, 4 * (size_t)B.max_nsol);
     take(B.o_err, 4);
+    B.base = off;
     // two steps per launch: node flags, and the workgroup table (eight lists, each
     // at most one run longer than the shortest)
     const bool pairs = es >= 4 && es * (size_t)pop_el >= kPairBytes;
@@ -545,7 +547,7 @@ lbm_status lbm_batch_create(const lbm_grid* grids, const double* taus, const lbm
         set_err(g_err, "workspace must be a non-NULL 256-byte aligned device pointer");
         return LBM_EINVAL;
     }
-    if (bytes < B.total) {
+    if (bytes < B.base) {
         set_err(g_err, "workspace too small: %zu < %zu bytes", bytes, B.total);
         return LBM_ESIZE;
     }
@@ -575,7 +577,7 @@ lbm_status lbm_batch_create(const lbm_grid* grids, const double* taus, const lbm
     b->o_err = B.o_err;
     b->o_flags = B.o_flags;
     b->o_ptiles = B.o_ptiles;
-    b->pairs = B.n_ptiles_max > 0;
+    b->pairs = B.n_ptiles_max > 0 && bytes >= B.total;  // (a buffer without room for the tables: single steps)
     b->conv_h.assign(n_cases, 0);
     b->err[0] = 0;
     // the working set decides the streaming mode of the update

@@ -357,3 +357,27 @@ def test_large_batch_takes_two_steps_per_launch(lbm_mod, dtype):
     same(b)
     same(plain)
     assert b.status()[2:] == plain.status()[2:]
+
+
+def test_workspace_without_two_step_tables(lbm_mod, monkeypatch):
+    """A buffer that holds the state but not the tables of the two-step update
+    is accepted, and the batch gives the same results."""
+    shapes = [(1001, 517), (900, 1024), (130, 700), (1024, 700)]
+    cases = [lc.make_case(nx, ny, 0.6 + 0.05 * k, walls_y=k % 2 == 0, gx=2e-6, u0=(0.02, 0.01),
+                          bodies=[lc.disc(0.4 * nx, 0.5 * ny, 6.3)], name=f"tables_{k}") for k, (nx, ny) in enumerate(shapes)]
+    assert sum(36 * nx * ny for nx, ny in shapes) >= 64 * 2 ** 20  # populations in FP32
+    full = lbm_mod.LatticeBatch(cases, dtype="f32")
+    query = lbm_mod.lbm_batch_workspace_bytes
+    nodes = sum(nx * ny for nx, ny in shapes)  # at most the node flags' bytes
+    monkeypatch.setattr(lbm_mod, "lbm_batch_workspace_bytes", lambda *a: query(*a) - nodes)
+    small = lbm_mod.LatticeBatch(cases, dtype="f32")
+    for batch in (full, small):
+        batch.step(7)
+        batch.run(20, 1e-30, 10)
+    for k in range(len(cases)):
+        for x, y in zip(full.fields(k), small.fields(k)):
+            assert bool((x == y).all()), k
+    assert full.status() == small.status()
+    monkeypatch.setattr(lbm_mod, "lbm_batch_workspace_bytes", lambda *a: query(*a) // 2)
+    with pytest.raises(lbm_mod.LBMError):
+        lbm_mod.LatticeBatch(cases, dtype="f32")
