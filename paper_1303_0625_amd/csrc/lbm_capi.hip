@@ -370,9 +370,9 @@ uint8_t* own_ptr(lbm_ctx* c, int k) {
     return wsp<uint8_t>(c, c->L.own[k]);
 }
 
-// Geometry that stays: no body translates (the second owner map then holds
-// the node flags, the second link buffer two more steps' force partials, and
-// both parities' link counts, velocities and rotations are alike).
+// Geometry that stays: no body translates (both parities' link counts,
+// velocities and rotations are alike; the second owner map and the second link
+// buffer are free).
 bool fixed_geometry(const lbm_ctx* c) { return c->L.n_movers == 0; }
 
 // Index of the current owner map, link list and link counts.
@@ -387,16 +387,19 @@ int geo(const lbm_ctx* c) { return fixed_geometry(c) ? 0 : c->cur; }
 // 1024 (72 MiB) 23.1 / 25.6 us, FP64 1001 x 517 (38 MiB) 15.1 / 14.4 us, 1024 x
 // 1024 (72 MiB) 20.1 / 23.9 us, 4096 x 2048 (576 MiB) 133 / 202 us.
 constexpr size_t kPairBytes = 64ull << 20;
-bool pairs(const lbm_ctx* c) {
-    return fixed_geometry(c) && !c->ibb && !c->mrt && !c->prof && (c->g.dtype == LBM_F64 || c->g.dtype == LBM_F32) &&
-           c->L.pbytes >= kPairBytes;
+
+// Whether the lattice may take two steps per launch under some boundary rule,
+// operator and mode: the second owner map then holds the node flags, and the
+// second link buffer two more steps' force partials.
+bool may_pair(const lbm_ctx* c) {
+    return fixed_geometry(c) && (c->g.dtype == LBM_F64 || c->g.dtype == LBM_F32) && c->L.pbytes >= kPairBytes;
 }
+
+bool pairs(const lbm_ctx* c) { return may_pair(c) && !c->ibb && !c->mrt && !c->prof; }
 
 // Steps whose force totals a launch (or a reader) forms: the launch before may
 // have taken two.
-int pending_steps(const lbm_ctx* c) {
-    return fixed_geometry(c) && (c->g.dtype == LBM_F64 || c->g.dtype == LBM_F32) ? 2 : 1;
-}
+int pending_steps(const lbm_ctx* c) { return may_pair(c) ? 2 : 1; }
 
 template <typename T>
 StepPtrs<T> step_ptrs(lbm_ctx* c) {
@@ -422,8 +425,8 @@ StepPtrs<T> step_ptrs(lbm_ctx* c) {
     sp.movers = wsp<int>(c, c->L.movers);
     sp.partial = wsp<double>(c, c->L.partial);
     // (a chunk's 96 bytes fit its share of the link capacity: a body's is at
-    // least 288 links, the walls' 6 nx, and an empty list still has 256 bytes)
-    sp.partial_b = fixed_geometry(c) ? wsp<double>(c, c->L.links[1]) : sp.partial;
+    // least 128 links, the walls' 6 nx, and an empty list still has 256 bytes)
+    sp.partial_b = may_pair(c) ? wsp<double>(c, c->L.links[1]) : sp.partial;
     sp.hist = wsp<double>(c, c->L.hist);
     sp.tctr = wsp<int64_t>(c, c->L.tctr);
     sp.errflag = wsp<int>(c, c->L.err);
@@ -467,9 +470,9 @@ lbm_status dispatch_pair(lbm_ctx* c) {
     return c->g.dtype == LBM_F64 ? enqueue_pair<double>(c) : enqueue_pair<float>(c);
 }
 
-// Node flags of a fixed geometry, from its owner map.
+// Node flags of a lattice that may take two steps per launch, from its owner map.
 void enqueue_flags(lbm_ctx* c) {
-    if (!fixed_geometry(c)) return;
+    if (!may_pair(c)) return;
     k_node_flags<<<(unsigned)node_blocks(c), kBlock, 0, c->stream>>>(own_ptr(c, 0), wsp<uint8_t>(c, c->L.own[1]),
                                                                      step_args(c));
 }

@@ -1543,7 +1543,7 @@ __device__ inline void wave_sum6(const double acc[6], double out[3]) {
 //   bounce-back), R the body centre.
 // Each thread sums a fixed strided subset, the wave and workgroup combine in
 // a fixed tree into partial[c].  The per-solid totals are formed later, in
-// chunk order, by finalize_forces (in the next launch), so no workgroup
+// chunk order, by finalize_last (in the next launch), so no workgroup
 // waits on another and the result is independent of scheduling.
 struct ForceShared {
     double red[kBlock / 64][6];
@@ -1632,20 +1632,6 @@ __device__ inline void force_role(int c, ForceShared& fs, const T* __restrict__ 
     }
 }
 
-// Per-solid totals of step `step` from its chunk partials, summed in chunk
-// order, into the history ring (one workgroup).
-__device__ inline void finalize_forces(const double* __restrict__ partial,
-                                       const int* __restrict__ solid_chunk0, double* __restrict__ hist,
-                                       int64_t step, const ForceArgs& a) {
-    const int64_t slot = step % a.hist_cap;
-    for (int r = threadIdx.x; r < a.nsol * 6; r += kBlock) {
-        const int sid = r / 6, q = r % 6;
-        double v = 0.0;
-        for (int cc = solid_chunk0[sid]; cc < solid_chunk0[sid + 1]; ++cc) v += partial[cc * 6 + q];
-        hist[(slot * a.nsol + sid) * 6 + q] = v;
-    }
-}
-
 // ------------------------------------------------------------------ fused step
 // One launch per time step: workgroups [0, n_force) are force chunks,
 // [n_force, n_force + n_move) are translating bodies, workgroup
@@ -1683,13 +1669,34 @@ struct StepPtrs {
     }
 };
 
-// Totals of the last `count` (1 or 2) steps before step t, oldest first (a
-// history of one step keeps the last).
+// Per-solid totals of the last `count` (1 or 2) steps before step t from their
+// chunk partials, summed in chunk order, into the history ring (one workgroup; a
+// history of one step keeps the last).  One thread per (step, solid, component):
+// a sum is a chain of loads, which two steps must not make twice as long, and
+// four loads are in flight at once.  Per step, one chain of single loads per
+// launch / two such chains in a row / now: 4096 x 128 FP32 channel (48 chunks of
+// wall links, one step per launch) 12.8 / 19.4 / 9.4 us; 400,000 x 16 (two steps
+// per launch) 722 / 1158 / 492 us.
 template <typename T>
 __device__ inline void finalize_last(const StepPtrs<T>& p, int64_t t, int count, const ForceArgs& a) {
-    for (int64_t u = t - count; u < t; ++u) {
-        if (u >= 0) finalize_forces(p.part(u, a.nchunks), p.solid_chunk0, p.hist, u, a);
-        __syncthreads();
+    const int rows = a.nsol * 6, steps = count < a.hist_cap ? count : (int)a.hist_cap;
+    for (int r = threadIdx.x; r < steps * rows; r += kBlock) {
+        const int k = r / rows, sid = (r - k * rows) / 6, q = r - k * rows - 6 * sid;
+        const int64_t u = t - steps + k;
+        if (u < 0) continue;
+        const int c0 = p.solid_chunk0[sid], c1 = p.solid_chunk0[sid + 1];
+        const double* at = p.part(u, a.nchunks) + (size_t)c0 * 6 + q;
+        double v = 0.0;
+        int n = c1 - c0;
+        for (; n >= 4; n -= 4, at += 24) {
+            const double v0 = at[0], v1 = at[6], v2 = at[12], v3 = at[18];
+            v += v0;
+            v += v1;
+            v += v2;
+            v += v3;
+        }
+        for (; n > 0; --n, at += 6) v += at[0];
+        p.hist[((u % a.hist_cap) * a.nsol + sid) * 6 + q] = v;
     }
 }
 

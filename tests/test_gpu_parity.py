@@ -666,3 +666,22 @@ def test_mover_box_repeats_body_columns(oracle_mod, lbm_mod, vx, cx):
         assert (lat.fields("f64")[3].cpu().numpy() == osim.fields()[3]).all(), lat.t
     compare_fields(lat, osim, 1e-12)
     compare_forces(lat, osim, c, 1e-10)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("nx,ny", [(40000, 60), (700, 61)])  # two steps per launch and many chunks; single steps
+def test_force_totals_of_short_histories(lbm_mod, dtype, nx, ny):
+    """The totals of a launch's steps go to a history of one, two or more steps
+    alike: the last step's forces of every solid are the same after odd and even
+    counts, with graphs and without."""
+    c = lc.make_case(nx, ny, 0.7, walls_y=True, gx=2e-6, u0=(0.02, 0.0), wall_v=(0.01, 0.0),
+                     bodies=[lc.disc(100.3 + 60 * k, 30.2, 4.1 + k, vx=0.01 * k) for k in range(4)], name="short_history")
+    lats = [lbm_mod.Lattice(c, dtype=dtype, history_steps=h) for h in (64, 1, 2, 3)]
+    for n in (1, 2, 3, 34):
+        for lat in lats:
+            lat.step(n)
+        want = [lats[0].force(s, k) for s in range(5) for k in (0, 1)]
+        assert np.isfinite(np.array(want)).all()
+        for lat in lats[1:]:
+            assert [lat.force(s, k) for s in range(5) for k in (0, 1)] == want, (lat.history_steps, lat.t)
+        assert bool((lats[3].force_history(lats[3].t - 1, 1) == lats[0].force_history(lats[0].t - 1, 1)).all())
