@@ -33,7 +33,7 @@ struct lbm_batch {
     int waves = 4;
     int nt = 1;
     int n_tiles = 0;
-    // two steps per launch (from kPairBytes of populations on): its workgroups
+    // two steps per launch (where the layout has its tables): its workgroups
     bool pairs = false;
     int n_ptiles = 0;
     std::vector<int> conv_h;  // host copy of the converged flags (at the last sync)
@@ -88,6 +88,7 @@ const char* batch_layout(const lbm_grid* grids, const double* taus, const lbm_so
     int64_t pop_el = 0;  // population elements of one buffer
     int64_t units = 0;  // workgroups of the two-step update
     int most = 0;       // of one run
+    PairWork work;
     int links = 0, sbase = 0;
     B.max_nsol = 1;
     B.n_tiles_max = 0;
@@ -162,6 +163,7 @@ const char* batch_layout(const lbm_grid* grids, const double* taus, const lbm_so
         d.pair = pair_args(g.nx, g.ny);
         units += (int64_t)d.pair.strips * d.pair.runs;
         most = std::max(most, d.pair.strips);
+        work.add(g.nx, g.ny, d.pair);
         // links and chunks: walls, then bodies
         int local = 0;
         d.chunk_first = (int)B.chunks.size();
@@ -215,7 +217,7 @@ const char* batch_layout(const lbm_grid* grids, const double* taus, const lbm_so
     B.base = off;
     // two steps per launch: node flags, and the workgroup table (eight lists, each
     // at most one run longer than the shortest)
-    const bool pairs = es >= 4 && es * (size_t)pop_el >= kPairBytes;
+    const bool pairs = es >= 4 && es * (size_t)pop_el >= kPairBytes && work.pays(grids[0].dtype);
     B.n_ptiles_max = pairs ? (int)(8 * (units / 8 + most + 1)) : 0;
     take(B.o_flags, pairs ? (size_t)own_off : 0);
     take(B.o_ptiles, sizeof(PairTile) * (size_t)B.n_ptiles_max);

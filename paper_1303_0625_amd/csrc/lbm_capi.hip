@@ -55,6 +55,45 @@ size_t dtype_size(int dt) {
     }
 }
 
+// Split of the two-step update: strips of equal width, at most kPairOut columns;
+// runs of about kPairRows rows, at least 4 (two waves of two).  Longer runs repeat
+// less work but keep more rows in flight at once, which costs more: 50 steps of
+// 4096 x 4096 FP32 with runs of 16 / 20 / 28 / 40 / 64 rows take 7.66 / 7.63 / 7.73 /
+// 8.18 / 9.15 ms.
+constexpr int kPairRows = 20;
+PairArgs pair_args(int nx, int ny) {
+    PairArgs a;
+    a.strips = (nx + kPairOut - 1) / kPairOut;
+    a.width = (nx + a.strips - 1) / a.strips;
+    a.strips = (nx + a.width - 1) / a.width;
+    a.runs = std::max(1, std::min((ny + kPairRows - 1) / kPairRows, ny / 4));
+    return a;
+}
+
+// Two steps per launch pay from 64 MiB of populations on.
+// Below that a launch has too few workgroups for its rows in series: per step,
+// two per launch against one, FP32 1024 x 1024 (36 MiB) 15.0 / 14.3 us, 2048 x
+// 1024 (72 MiB) 19.9 / 24.3 us, FP64 1001 x 517 (38 MiB) 15.1 / 14.4 us, 1024 x
+// 1024 (72 MiB) 17.4 / 24.3 us, 4096 x 2048 (576 MiB) 133 / 202 us.
+constexpr size_t kPairBytes = 64ull << 20;
+
+// And where they keep the lanes busy: rows of waves of the one-step update
+// against those of the two-step update, whose strips have a wave each and whose
+// runs cost their rows and about sixteen more (four waves start, and finish the
+// rows where they meet).  Per step, two per launch against one, by the share
+// one / two: FP32 batches of 64 x 64 cases (0.25) 82 / 62 us, 128 x 64 (0.33) 68 /
+// 62, 320 x 24 (0.357) 27.0 / 25.6, 128 x 96 (0.364) 24.7 / 25.1, 192 x 64 (0.38)
+// 24.7 / 25.4, 56 x 96 (0.55) 35 / 62; FP64, bound by its bytes sooner: 64 x 24 (0.21)
+// 167 / 150, 64 x 64 (0.25) 62.9 / 61.2, 120 x 24 (0.29) 25.5 / 25.8.
+struct PairWork {
+    double one = 0.0, two = 0.0;
+    void add(int nx, int ny, const PairArgs& a) {
+        one += (double)((nx + 63) / 64) * ny;
+        two += (double)a.strips * (ny + 16.0 * a.runs);
+    }
+    bool pays(int dtype) const { return one >= (dtype == LBM_F64 ? 0.26 : 0.36) * two; }
+};
+
 // Workspace layout (byte offsets inside the caller's buffer).
 struct Layout {
     int pitch, opitch;
@@ -63,6 +102,7 @@ struct Layout {
         all, chunk_solid, chunk_start, solid_chunk0, partial, hist, tctr, err, total;
     int64_t link_total;
     int n_movers;  // bodies whose geometry moves (prescribed or free)
+    bool pair;     // two steps per launch under some boundary rule, operator and mode
     int nchunks;
     int box_bytes;  // LDS byte map per translating body (mover role)
     size_t fbytes;  // bytes of one population buffer
@@ -123,6 +163,9 @@ bool make_layout(const lbm_grid& g, const lbm_solid* solids, int n, int64_t hist
     }
     L.n_movers = 0;
     for (int k = 0; k < n; ++k) L.n_movers += solids[k].moves ? 1 : 0;
+    PairWork work;
+    work.add(g.nx, g.ny, pair_args(g.nx, g.ny));
+    L.pair = L.n_movers == 0 && es >= 4 && fbytes >= kPairBytes && work.pays(g.dtype);
     for (int k = 0; k < 2; ++k) {
         L.own[k] = off;
         off = align256(off + (size_t)g.ny * L.opitch);
@@ -378,28 +421,16 @@ bool fixed_geometry(const lbm_ctx* c) { return c->L.n_movers == 0; }
 // Index of the current owner map, link list and link counts.
 int geo(const lbm_ctx* c) { return fixed_geometry(c) ? 0 : c->cur; }
 
-// Two steps per launch: fixed geometry, half-way bounce-back, BGK, FP64 or FP32
-// storage (profiling times single steps), and populations of at least 64 MiB.
-// (MRT: the compiler's own contraction of collide_mrt differs between the two
-// kernels in the last bit of FP64.)
-// Below that a launch has too few workgroups for its rows in series: per step,
-// two per launch against one, FP32 1024 x 1024 (36 MiB) 15.0 / 14.3 us, 2048 x
-// 1024 (72 MiB) 23.1 / 25.6 us, FP64 1001 x 517 (38 MiB) 15.1 / 14.4 us, 1024 x
-// 1024 (72 MiB) 20.1 / 23.9 us, 4096 x 2048 (576 MiB) 133 / 202 us.
-constexpr size_t kPairBytes = 64ull << 20;
-
-// Whether the lattice may take two steps per launch under some boundary rule,
-// operator and mode: the second owner map then holds the node flags, and the
-// second link buffer two more steps' force partials.
-bool may_pair(const lbm_ctx* c) {
-    return fixed_geometry(c) && (c->g.dtype == LBM_F64 || c->g.dtype == LBM_F32) && c->L.pbytes >= kPairBytes;
-}
-
-bool pairs(const lbm_ctx* c) { return may_pair(c) && !c->ibb && !c->mrt && !c->prof; }
+// Two steps per launch: lattices of the layout's choice (their second owner map
+// holds the node flags, the second link buffer two more steps' force partials)
+// under half-way bounce-back and BGK; profiling times single steps.  (MRT: the
+// compiler's own contraction of collide_mrt differs between the two kernels in
+// the last bit of FP64.)
+bool pairs(const lbm_ctx* c) { return c->L.pair && !c->ibb && !c->mrt && !c->prof; }
 
 // Steps whose force totals a launch (or a reader) forms: the launch before may
 // have taken two.
-int pending_steps(const lbm_ctx* c) { return may_pair(c) ? 2 : 1; }
+int pending_steps(const lbm_ctx* c) { return c->L.pair ? 2 : 1; }
 
 template <typename T>
 StepPtrs<T> step_ptrs(lbm_ctx* c) {
@@ -426,26 +457,11 @@ StepPtrs<T> step_ptrs(lbm_ctx* c) {
     sp.partial = wsp<double>(c, c->L.partial);
     // (a chunk's 96 bytes fit its share of the link capacity: a body's is at
     // least 128 links, the walls' 6 nx, and an empty list still has 256 bytes)
-    sp.partial_b = may_pair(c) ? wsp<double>(c, c->L.links[1]) : sp.partial;
+    sp.partial_b = c->L.pair ? wsp<double>(c, c->L.links[1]) : sp.partial;
     sp.hist = wsp<double>(c, c->L.hist);
     sp.tctr = wsp<int64_t>(c, c->L.tctr);
     sp.errflag = wsp<int>(c, c->L.err);
     return sp;
-}
-
-// Split of the two-step update: strips of equal width, at most kPairOut columns;
-// runs of about kPairRows rows, at least 4 (two waves of two).  Longer runs repeat
-// less work but keep more rows in flight at once, which costs more: 50 steps of
-// 4096 x 4096 FP32 with runs of 16 / 20 / 28 / 40 / 64 rows take 7.66 / 7.63 / 7.73 /
-// 8.18 / 9.15 ms.
-constexpr int kPairRows = 20;
-PairArgs pair_args(int nx, int ny) {
-    PairArgs a;
-    a.strips = (nx + kPairOut - 1) / kPairOut;
-    a.width = (nx + a.strips - 1) / a.strips;
-    a.strips = (nx + a.width - 1) / a.width;
-    a.runs = std::max(1, std::min((ny + kPairRows - 1) / kPairRows, ny / 4));
-    return a;
 }
 
 // Enqueue two time steps (pairs()): one launch.
@@ -472,7 +488,7 @@ lbm_status dispatch_pair(lbm_ctx* c) {
 
 // Node flags of a lattice that may take two steps per launch, from its owner map.
 void enqueue_flags(lbm_ctx* c) {
-    if (!may_pair(c)) return;
+    if (!c->L.pair) return;
     k_node_flags<<<(unsigned)node_blocks(c), kBlock, 0, c->stream>>>(own_ptr(c, 0), wsp<uint8_t>(c, c->L.own[1]),
                                                                      step_args(c));
 }

@@ -124,3 +124,33 @@ def plane_state(oracle_mod, osim, own):
     mask[:, :, 0] = (own[:, :, 0] == 0) & (own[:, :, 1] == 0)
     mask[:, :, -1] = (own[:, :, -1] == 0) & (own[:, :, -2] == 0)
     return rho, u, mask
+
+
+def words_apart(a, b, dtype):
+    """Words of the storage type's size that differ between two workspaces."""
+    import torch
+
+    t = {"f64": torch.int64, "f32": torch.int32, "f16": torch.int16, "bf16": torch.int16}[dtype]
+    n = min(a.numel(), b.numel()) // 8 * 8
+    return int((a[:n].view(t) != b[:n].view(t)).sum())
+
+
+def zeroed_workspaces(monkeypatch):
+    """Workspaces allocated from here on start as zeros (a freed one of the same
+    layout could otherwise come back with a state in both buffers)."""
+    import torch
+
+    monkeypatch.setattr(torch, "empty", torch.zeros)
+
+
+def steps_per_launch(lat, dtype):
+    """Whether a fresh lattice in a zeroed workspace takes its next two steps in
+    one launch or two: one launch writes one of the two population buffers, two
+    write both.  (Every population of the lattice has to change in every step.)"""
+    before = lat.workspace.clone()
+    lat.step(2)
+    lat.stream.synchronize()
+    pops = 9 * lat.nx * lat.ny
+    changed = words_apart(before, lat.workspace, dtype) / pops
+    assert 0.8 < changed < 1.2 or 1.7 < changed, changed
+    return 2 if changed < 1.2 else 1

@@ -381,3 +381,34 @@ def test_workspace_without_two_step_tables(lbm_mod, monkeypatch):
     monkeypatch.setattr(lbm_mod, "lbm_batch_workspace_bytes", lambda *a: query(*a) // 2)
     with pytest.raises(lbm_mod.LBMError):
         lbm_mod.LatticeBatch(cases, dtype="f32")
+
+
+@pytest.mark.parametrize("n,nx,ny,dtype,want", [
+    (150, 256, 128, "f32", 2),
+    (50, 256, 128, "f32", 1),    # 56 MiB of populations
+    (600, 64, 64, "f32", 1),     # two strips where one wave holds a row
+    (300, 128, 64, "f32", 1),    # three strips for two waves, runs of 16 rows
+    (200, 128, 96, "f32", 2),
+    (500, 56, 64, "f32", 2),
+    (300, 64, 64, "f64", 1),
+    (150, 128, 64, "f64", 2),
+    (400, 256, 64, "f16", 1)])
+def test_which_batches_take_two_steps_per_launch(lbm_mod, monkeypatch, n, nx, ny, dtype, want):
+    """The choice between one and two steps per launch, seen from the state:
+    after four steps the buffer that is not current holds the state of step 3
+    (as after three steps, which are single) or, after two double steps, that
+    of step 2."""
+    from tests.helpers import words_apart, zeroed_workspaces
+
+    zeroed_workspaces(monkeypatch)
+    cases = [lc.make_case(nx, ny, 0.7, walls_y=True, gx=1e-4, gy=2e-4, u0=(0.02, 0.01),
+                          bodies=[lc.disc(0.4 * nx, 0.5 * ny, 5.3, vx=0.01)], name="pairs")] * n
+    _say(f"{n} x {nx}x{ny} {dtype}")
+    a, b = (lbm_mod.LatticeBatch(cases, dtype=dtype) for _ in range(2))
+    a.step(4)
+    b.step(3)
+    off = a._ws_ptr - a.workspace.data_ptr(), b._ws_ptr - b.workspace.data_ptr()
+    size = a.workspace.numel() - 256
+    changed = words_apart(a.workspace[off[0]:off[0] + size], b.workspace[off[1]:off[1] + size], dtype) / (9 * n * nx * ny)
+    assert 0.8 < changed < 1.2 or 1.7 < changed, changed
+    assert (2 if changed > 1.7 else 1) == want

@@ -685,3 +685,56 @@ def test_force_totals_of_short_histories(lbm_mod, dtype, nx, ny):
         for lat in lats[1:]:
             assert [lat.force(s, k) for s in range(5) for k in (0, 1)] == want, (lat.history_steps, lat.t)
         assert bool((lats[3].force_history(lats[3].t - 1, 1) == lats[0].force_history(lats[0].t - 1, 1)).all())
+
+
+@pytest.mark.parametrize("nx,ny,dtype,kw,want", [
+    (2048, 1024, "f32", {}, 2),                   # 72 MiB of populations
+    (1024, 1024, "f32", {}, 1),                   # 36 MiB
+    (1024, 1024, "f64", {}, 2),
+    (56, 29201, "f32", {}, 2),                    # one strip
+    (57, 30000, "f32", {}, 1),                    # two strips where one wave holds a row
+    (64, 29200, "f32", {}, 1),
+    (64, 14600, "f64", {}, 2),                    # (bound by its bytes sooner)
+    (113, 15007, "f32", {}, 2),                   # three strips, two waves
+    (4200000, 4, "f64", {}, 1),                   # runs of four rows
+    (2048, 1024, "f32", {"mrt": (1.64, 1.54, 1.9)}, 1),
+    (2048, 1024, "f32", {"ibb": True}, 1),
+    (2048, 1024, "f32", {"moves": True}, 1),
+    (2048, 1024, "f32", {"profile": True}, 1),
+    (4096, 2048, "f16", {}, 1)])
+def test_which_lattices_take_two_steps_per_launch(lbm_mod, monkeypatch, nx, ny, dtype, kw, want):
+    """The choice between one and two steps per launch, seen from the buffers
+    that two steps write."""
+    from tests.helpers import steps_per_launch, zeroed_workspaces
+
+    zeroed_workspaces(monkeypatch)
+    bodies = [lc.disc(0.4 * nx, 0.5 * ny, 5.3, vx=0.01, moves=kw.get("moves", False))] if min(nx, ny) > 40 else []
+    c = lc.make_case(nx, ny, 0.7, walls_y=True, gx=1e-4, gy=2e-4, u0=(0.02, 0.01), bodies=bodies, name="pairs")
+    lat = lbm_mod.Lattice(c, dtype=dtype, history_steps=4, mrt=kw.get("mrt"))
+    if kw.get("ibb"):
+        lat.set_boundary(True)
+    if kw.get("profile"):
+        lat.profile(True)
+    _say(f"{nx}x{ny} {dtype} {kw}")
+    assert steps_per_launch(lat, dtype) == want
+
+
+@pytest.mark.parametrize("dtype,nx,ny", [("f64", 64, 14600), ("f64", 57, 14600), ("f64", 128, 7400), ("f32", 113, 15007),
+                                         ("f32", 56, 29201), ("f32", 65, 14601), ("f32", 2048, 1027)])
+def test_two_steps_in_one_launch_equal_two(lbm_mod, monkeypatch, dtype, nx, ny):
+    """Lattices seen to take two steps per launch equal single steps (the
+    profiling mode) bit for bit, populations and forces."""
+    from tests.helpers import steps_per_launch, zeroed_workspaces
+
+    zeroed_workspaces(monkeypatch)
+    c = _pair_case(nx, ny, True, nx + ny)
+    a = lbm_mod.Lattice(c, dtype=dtype, history_steps=64)
+    b = lbm_mod.Lattice(c, dtype=dtype, history_steps=64)
+    assert steps_per_launch(a, dtype) == 2
+    b.profile(True)
+    b.step(2)
+    for n in (0, 1, 3, 34):
+        a.step(n)
+        b.step(n)
+        assert bool((a.populations() == b.populations()).all()), (nx, ny, a.t)
+        assert bool((a.force_history() == b.force_history()).all()), (nx, ny, a.t)
