@@ -13,21 +13,24 @@
 
 namespace lbm {
 
-struct CaseDev {
-    StepArgs sa;            // lattice shape and strides
-    CollideParams<double> cp64;
-    CollideParams<float> cp32;
-    ForceArgs fa;           // force arguments (hist unused)
-    int64_t f_off[2];       // element offsets of the two population buffers
-    int64_t own_off;        // byte offset of the owner map
-    int64_t snap_off;       // element offset of the velocity snapshot [2][ny][nx]
-    int links_base;         // first link of the case in the global link array
-    int solid_base;         // first solid record / vtab entry of the case
-    int nsol;               // bodies + 1
-    int chunk_first, chunk_count;  // force chunks of the case
+// A case's parameters, those of the step first and from a cache line's start: a
+// workgroup reads its case's anew, and the lines it touches are part of its latency
+// (in the order of their subjects: 2% more per step of 20 to 72 MiB of cases).
+struct alignas(64) CaseDev {
     int wpr;                // waves per row (rowlen / 64)
     int nwaves;             // ny * wpr
+    int solid_base;         // first solid record / vtab entry of the case
+    int nsol;               // bodies + 1
+    int64_t f_off[2];       // element offsets of the two population buffers
+    int64_t own_off;        // byte offset of the owner map
+    StepArgs sa;            // lattice shape and strides
+    CollideParams<double> cp64;
     PairArgs pair;          // split of the two-step update
+    CollideParams<float> cp32;
+    ForceArgs fa;           // force arguments (hist unused)
+    int64_t snap_off;       // element offset of the velocity snapshot [2][ny][nx]
+    int links_base;         // first link of the case in the global link array
+    int chunk_first, chunk_count;  // force chunks of the case
 };
 
 // Update tile: `waves` consecutive waves of one case, starting at wave0.
@@ -60,15 +63,20 @@ __global__ __launch_bounds__(WAVES * 64) void k_batch_step(const CaseDev* __rest
     if (blockIdx.x == 0 && threadIdx.x == 0 && tdev) tdev[parity ^ 1] = tdev[parity] + 1;
     if (converged[tl.c]) return;
     const CaseDev& cd = cases[tl.c];
+    // (copies: read together, beside the populations' loads, and not again after
+    // every store; read where they are used they cost three round trips in a row,
+    // 26.4 us per step of 72 MiB of FP32 cases against 25.6, FP16 75 against 38)
+    const CollideParams<typename Sto<T>::C> cp = case_cp<T>(cd);
+    const StepArgs sa = cd.sa;
     const int w = tl.wave0 + (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (w >= cd.nwaves) return;
     const int y = w / cd.wpr;
     const int x = (w - y * cd.wpr) * 64 + (int)(threadIdx.x & 63);
     if constexpr (!Sto<T>::kSplit) {
-        if (x >= cd.sa.nx) return;
+        if (x >= sa.nx) return;
     }
     step_node<T, NT>(x, y, fbase + cd.f_off[parity], fbase + cd.f_off[parity ^ 1], obase + cd.own_off,
-                     vtab_all + 2 * cd.solid_base, nullptr, nullptr, 0, cd.sa, case_cp<T>(cd), nullptr, x < cd.sa.nx);
+                     vtab_all + 2 * cd.solid_base, nullptr, nullptr, 0, sa, cp, nullptr, x < sa.nx);
 }
 
 // Two time steps of every listed workgroup of the two-step update (strip and run
