@@ -461,6 +461,9 @@ lbm_status batch_reset(lbm_batch* b) {
     std::vector<CaseResult> res(b->n, CaseResult{0, 0, 0, -1.0});
     BCHK(b, hipMemcpyAsync(b->ws + b->o_conv, b->conv_h.data(), 4 * (size_t)b->n, hipMemcpyHostToDevice, st));
     BCHK(b, hipMemcpyAsync(b->ws + b->o_res, res.data(), sizeof(CaseResult) * b->n, hipMemcpyHostToDevice, st));
+    // (a case that no check has met yet has no force: zeros, not what the buffer held)
+    const std::vector<double> none((size_t)b->n * b->max_nsol * 6, 0.0);
+    BCHK(b, hipMemcpyAsync(b->ws + b->o_forces, none.data(), 8 * none.size(), hipMemcpyHostToDevice, st));
     k_set_counters<<<1, 1, 0, st>>>(bws<int64_t>(b, b->o_tdev), 0, bws<int>(b, b->o_err));
     for (int c = 0; c < b->n; ++c) batch_init_dispatch(b, c, st, nullptr, nullptr, nullptr, LBM_F64);
     BCHK(b, hipGetLastError());

@@ -412,3 +412,26 @@ def test_which_batches_take_two_steps_per_launch(lbm_mod, monkeypatch, n, nx, ny
     changed = words_apart(a.workspace[off[0]:off[0] + size], b.workspace[off[1]:off[1] + size], dtype) / (9 * n * nx * ny)
     assert 0.8 < changed < 1.2 or 1.7 < changed, changed
     assert (2 if changed > 1.7 else 1) == want
+
+
+def test_forces_before_the_first_check_are_zero(lbm_mod, monkeypatch):
+    """A case that no check has met reports zero force, whatever its workspace
+    held before."""
+    import torch
+
+    empty = torch.empty
+
+    def dirty(*a, **k):
+        t = empty(*a, **k)
+        return t.fill_(0x3f) if t.dtype == torch.uint8 else t
+
+    monkeypatch.setattr(torch, "empty", dirty)
+    case = uneven_cases()[0]
+    batch = lbm_mod.LatticeBatch([case, case], dtype="f64")
+    assert batch.status()[3] == [(0.0, 0.0)] * 2
+    batch.step(10)
+    batch.set_active(1, False)
+    batch.run(20, 1e-30, 10)
+    drag = batch.status()[3]
+    assert drag[0][0] != 0.0 and drag[1] == (0.0, 0.0)
+    assert tuple(batch.force(1, 1, 0)) == (0.0, 0.0, 0.0)
