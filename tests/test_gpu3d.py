@@ -473,3 +473,25 @@ def test_moving_sphere_box_tiles_f64(oracle_mod, lbm_mod, shape, spheres, ibb):
     er, eu = field_err(lat, osim)
     assert er <= 1e-12 and eu <= 1e-12
     assert force_err(lat, osim) <= 1e-10
+
+
+@pytest.mark.parametrize("n", [63, 64, 65, 150])
+def test_suspension_of_many_spheres_f64(oracle_mod, lbm_mod, n):
+    """Spheres of a suspension around the numbers that fill a word of the tiles'
+    sphere lists, some at rest, across the periodic boundaries: FP64 fields,
+    owners and forces against the oracle."""
+    rng = np.random.default_rng(n)
+    spheres = []
+    for k in range(n):
+        x, y, z = k % 6, k // 6 % 5, k // 30
+        p = np.array([7.0 * x, 7.0 * y, 7.0 * z]) + rng.uniform(-0.4, 0.4, 3)
+        rest = k % 10 == 3
+        spheres.append(dict(cx=float(p[0] % 42), cy=float(p[1] % 35), cz=float(p[2] % 35), r=float(rng.uniform(1.2, 1.7)),
+                            v=(0.0, 0.0, 0.0) if rest else (0.05, -0.03, 0.04), moves=not rest))
+    c = dict(name=f"suspension_{n}", nx=42, ny=35, nz=35, tau=0.8, u0=(0.045, -0.025, 0.035), g=(1e-5, 0.0, 0.0),
+             spheres=spheres)
+    lat, osim = run_pair(oracle_mod, lbm_mod, c, 14)
+    assert osim.error == 0
+    er, eu = field_err(lat, osim)
+    assert er <= 1e-12 and eu <= 1e-12
+    assert force_err(lat, osim) <= 1e-10
