@@ -299,9 +299,10 @@ int pitch_for(int nx) { return (nx + 63) / 64 * 64; }
 using StepKernel = void (*)(Ptrs, int, int, Args);
 
 template <typename T, bool NT>
-StepKernel step_kernel(bool ibb, bool pressure) {
-    if (ibb) return pressure ? k3_step<T, NT, true, true> : k3_step<T, NT, true, false>;
-    return pressure ? k3_step<T, NT, false, true> : k3_step<T, NT, false, false>;
+StepKernel step_kernel(bool ibb, bool pressure, bool move) {
+    if (move) return ibb ? k3_step<T, NT, true, false, true> : k3_step<T, NT, false, false, true>;
+    if (ibb) return pressure ? k3_step<T, NT, true, true, false> : k3_step<T, NT, true, false, false>;
+    return pressure ? k3_step<T, NT, false, true, false> : k3_step<T, NT, false, false, false>;
 }
 
 }  // namespace
@@ -528,10 +529,10 @@ lbm_status lbm3d_step(lbm3d_ctx* c, int64_t n) {
         if (timed) HIPCHK3(c, hipEventRecord(c->ev[c->ev_used], c->stream));
         {
             // the pressure planes, when set, are part of the step launch
-            const bool ibb = c->ibb != 0, pr = c->pressure != 0;
+            const bool ibb = c->ibb != 0, pr = c->pressure != 0, mv = c->L.nmovers > 0;
             const StepKernel kern = c->g.dtype == LBM_F64
-                                        ? (nt ? step_kernel<double, true>(ibb, pr) : step_kernel<double, false>(ibb, pr))
-                                        : (nt ? step_kernel<float, true>(ibb, pr) : step_kernel<float, false>(ibb, pr));
+                                        ? (nt ? step_kernel<double, true>(ibb, pr, mv) : step_kernel<double, false>(ibb, pr, mv))
+                                        : (nt ? step_kernel<float, true>(ibb, pr, mv) : step_kernel<float, false>(ibb, pr, mv));
             kern<<<grid, kBlock, c->L.nmovers > 0 ? 2 * kBoxLinks : 0, c->stream>>>(p, par, n_lead, a);
         }
         double* sol_n = at<double>(c, c->L.sol[par ^ 1]);

@@ -90,14 +90,21 @@ __device__ inline void centre3(const double* __restrict__ sol, int s, int64_t t,
     for (int d = 0; d < 3; ++d) X[d] = mv ? S[d] + (double)t * S[4 + d] : S[d];
 }
 
-// (a difference well inside the half period is its own image: floor gives 0)
+// Minimum image of a difference.  SHORT: a difference well inside the half period
+// is its own image (floor gives 0), without the division.  That saves the
+// interpolated step's link code a fifth of its time (tube of 96 nodes with a sphere
+// of r = 23, per step: 44.4 us, 36.9) and its kernel the registers of a fourth wave
+// per SIMD; where a division is all that a link costs, the branch costs more than
+// it (half-way step, 27 spheres in 96^3: 63.4 us with the division, 68.0 without).
+template <bool SHORT = false>
 __device__ inline double min_image3(double d, int n) {
-    if (fabs(d) < 0.49 * (double)n) return d;
+    if (SHORT && fabs(d) < 0.49 * (double)n) return d;
     return d - (double)n * floor(d / (double)n + 0.5);
 }
 
 // Rigid surface velocity of solid slot s at point p at step t (duct at
 // rest), and the arm from the centre.
+template <bool SHORT = false>
 __device__ inline void surface_vel(const double* __restrict__ sol, int s, int64_t t, double px, double py,
                                    double pz, const Args& a, double v[3], double r[3]) {
     if (s == 0) {
@@ -108,9 +115,9 @@ __device__ inline void surface_vel(const double* __restrict__ sol, int s, int64_
     const double* S = sol + kSolidRow * s;
     double X[3];
     centre3(sol, s, t, X);
-    r[0] = min_image3(px - X[0], a.nx);
-    r[1] = min_image3(py - X[1], a.ny);
-    r[2] = min_image3(pz - X[2], a.nz);
+    r[0] = min_image3<SHORT>(px - X[0], a.nx);
+    r[1] = min_image3<SHORT>(py - X[1], a.ny);
+    r[2] = min_image3<SHORT>(pz - X[2], a.nz);
     v[0] = S[4] + (S[8] * r[2] - S[9] * r[1]);
     v[1] = S[5] + (S[9] * r[0] - S[7] * r[2]);
     v[2] = S[6] + (S[7] * r[1] - S[8] * r[0]);
@@ -135,12 +142,13 @@ __device__ inline double tube_q3(int y, int z, int ey, int ez, const Args& a) {
 // Fraction q in (0, 1] of the link from node (x, y, z) along e into sphere
 // slot s at step t: the nearer root of |P + q e| = r with P the node's
 // minimum-image offset from the centre (half-coefficient form), clamped.
+template <bool SHORT = false>
 __device__ inline double sphere_q3(const double* __restrict__ sol, int s, int64_t t, int x, int y, int z, int ex,
                                    int ey, int ez, const Args& a) {
     double X[3];
     centre3(sol, s, t, X);
-    const double px = min_image3((double)x - X[0], a.nx), py = min_image3((double)y - X[1], a.ny),
-                 pz = min_image3((double)z - X[2], a.nz);
+    const double px = min_image3<SHORT>((double)x - X[0], a.nx), py = min_image3<SHORT>((double)y - X[1], a.ny),
+                 pz = min_image3<SHORT>((double)z - X[2], a.nz);
     const double r = sol[kSolidRow * s + 3];
     const double e2 = (double)(ex * ex + ey * ey + ez * ez);
     const double pe = px * ex + py * ey + pz * ez;
@@ -216,7 +224,9 @@ struct Ptrs {
 // with v at the link midpoint; CME F = e_i (a + b), GME F = (e_i - v) a +
 // (e_i + v) b; torque r x F about the sphere's centre.
 // IBB: interpolated bounce-back may be on (a.ibb); without it the link code
-// (and the kernel's registers) stay those of half-way bounce-back.
+// (and the kernel's registers) stay those of half-way bounce-back.  MOVE: spheres
+// may move; without it the search of their boxes is left out (64^3 with a sphere
+// of r = 15 at rest: 20.4 us per step with it, 20.0).
 //
 // A moving sphere has no link list: a workgroup takes kChunk nodes of its scan
 // box, two neighbouring ones per thread, finds each node's links from nineteen
@@ -252,13 +262,13 @@ __device__ inline void wave_sum12(const double acc[12], double out[3]) {
         for (int q = 0; q < 3; ++q) out[q] += __shfl_xor(out[q], off, 64);
 }
 
-template <typename T, bool IBB>
+template <typename T, bool IBB, bool MOVE>
 __device__ inline void force_role3(int c, const Ptrs& p, double* __restrict__ partial, const Args& a,
                                    double (*red)[12], uint16_t* __restrict__ list, int64_t t) {
     const T* f = (const T*)p.fin;
     const int s = p.chunk_solid[c];
     const int start = p.chunk_start[c];
-    const bool box = s > 0 && p.sol[kSolidRow * s + 10] != 0.0;
+    const bool box = MOVE && s > 0 && p.sol[kSolidRow * s + 10] != 0.0;
     int bx0 = 0, by0 = 0, bz0 = 0;
     int end = 0, first = start;
     auto box_node = [&](int k, int& x, int& y, int& z) {
@@ -328,11 +338,11 @@ __device__ inline void force_role3(int c, const Ptrs& p, double* __restrict__ pa
         // surface point x_f + q e_i (q = 1/2 unless interpolated on a sphere)
         double q = 0.5;
         if constexpr (IBB) {
-            if (a.ibb && s > 0) q = sphere_q3(p.sol, s, t, x, y, z, kE[i][0], kE[i][1], kE[i][2], a);
+            if (a.ibb && s > 0) q = sphere_q3<IBB>(p.sol, s, t, x, y, z, kE[i][0], kE[i][1], kE[i][2], a);
             if (a.ibb && s == 0 && a.duct == 1) q = tube_q3(y, z, kE[i][1], kE[i][2], a);
         }
         double v[3], r[3];
-        surface_vel(p.sol, s, t, x + q * ex, y + q * ey, z + q * ez, a, v, r);
+        surface_vel<IBB>(p.sol, s, t, x + q * ex, y + q * ey, z + q * ez, a, v, r);
         const double av =
             w * a.rho0 + (double)Sto<T>::ld(f[((int64_t)line * kQ + i) * a.pitch + x]);
         const double m = 6.0 * w * a.rho0 * (ex * v[0] + ey * v[1] + ez * v[2]);
@@ -503,10 +513,10 @@ __device__ inline void update3(int xo, int y, int z, const Ptrs& p, const Args& 
                     // interpolated bounce-back (spheres and tube): surface
                     // point x - q e_i; the node behind, x + e_i, is the source
                     // of o = opp(i), so d[o] still holds its value when fluid
-                    const double q = s > 0 ? sphere_q3(p.sol, s, t, x, y, z, -kE[i][0], -kE[i][1], -kE[i][2], a)
+                    const double q = s > 0 ? sphere_q3<IBB>(p.sol, s, t, x, y, z, -kE[i][0], -kE[i][1], -kE[i][2], a)
                                            : tube_q3(y, z, -kE[i][1], -kE[i][2], a);
                     double v[3], r[3];
-                    surface_vel(p.sol, s, t, x - q * kE[i][0], y - q * kE[i][1], z - q * kE[i][2], a, v, r);
+                    surface_vel<IBB>(p.sol, s, t, x - q * kE[i][0], y - q * kE[i][1], z - q * kE[i][2], a, v, r);
                     const double m = 6.0 * w3(i) * a.rho0 * (kE[i][0] * v[0] + kE[i][1] * v[1] + kE[i][2] * v[2]);
                     const int o = opp3(i);
                     d[i] = lbm::ibb_value<double>(q, own_val(o), own_val(i), d[o], src[o] == 0, m);
@@ -514,7 +524,7 @@ __device__ inline void update3(int xo, int y, int z, const Ptrs& p, const Args& 
                 }
             }
             double v[3], r[3];
-            surface_vel(p.sol, s, t, x - 0.5 * kE[i][0], y - 0.5 * kE[i][1], z - 0.5 * kE[i][2], a, v, r);
+            surface_vel<IBB>(p.sol, s, t, x - 0.5 * kE[i][0], y - 0.5 * kE[i][1], z - 0.5 * kE[i][2], a, v, r);
             d[i] = own_val(opp3(i)) + 6.0 * w3(i) * a.rho0 * (kE[i][0] * v[0] + kE[i][1] * v[1] + kE[i][2] * v[2]);
         }
     }
@@ -558,7 +568,7 @@ __device__ inline void update3(int xo, int y, int z, const Ptrs& p, const Args& 
 // Workgroups [0, nchunks) force chunks, the next (ns + 1) * 12 the previous
 // step's totals (the first also advances the step counter), update
 // workgroups from n_lead (a multiple of 8) on.
-template <typename T, bool NT, bool IBB, bool PR>
+template <typename T, bool NT, bool IBB, bool PR, bool MOVE>
 __global__ __launch_bounds__(kBlock) void k3_step(Ptrs p, int parity, int n_lead, Args a) {
     __shared__ double red[kBlock / 64][12];
     extern __shared__ uint16_t box_links[];  // kBoxLinks entries when a sphere moves
@@ -566,7 +576,7 @@ __global__ __launch_bounds__(kBlock) void k3_step(Ptrs p, int parity, int n_lead
     if (b < n_lead) {
         const int64_t t = p.tctr[parity];
         if (b < a.nchunks) {
-            force_role3<T, IBB>(b, p, p.partial + (size_t)(t & 1) * a.nchunks * 12, a, red, box_links, t);
+            force_role3<T, IBB, MOVE>(b, p, p.partial + (size_t)(t & 1) * a.nchunks * 12, a, red, box_links, t);
         } else if (b < a.nchunks + (a.ns + 1) * 12) {
             const int pair = b - a.nchunks;
             if (t >= 1)
