@@ -558,10 +558,10 @@ lbm_status lbm3d_step(lbm3d_ctx* c, int64_t n) {
             const int tiles = (c->L.box + kTileX - 1) / kTileX;
             const unsigned nb = (unsigned)(2 * tiles * tiles * tiles * c->L.nmovers);
             const int* mv = at<int>(c, c->L.movers);
-            if (c->g.dtype == LBM_F64)
-                k3_move<double><<<nb, kBlock, 0, c->stream>>>(p, sol_n, own_n, flags_n, mv, tiles, par, a);
-            else
-                k3_move<float><<<nb, kBlock, 0, c->stream>>>(p, sol_n, own_n, flags_n, mv, tiles, par, a);
+            const bool many = c->ns > kFewSpheres;
+            auto* move = c->g.dtype == LBM_F64 ? (many ? k3_move<double, true> : k3_move<double, false>)
+                                               : (many ? k3_move<float, true> : k3_move<float, false>);
+            move<<<nb, kBlock, 0, c->stream>>>(p, sol_n, own_n, flags_n, mv, tiles, par, a);
         }
         if (timed) {
             HIPCHK3(c, hipEventRecord(c->ev[c->ev_used + 1], c->stream));
