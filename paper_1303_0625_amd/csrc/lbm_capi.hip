@@ -429,8 +429,8 @@ int geo(const lbm_ctx* c) { return fixed_geometry(c) ? 0 : c->cur; }
 bool pairs(const lbm_ctx* c) { return c->L.pair && !c->ibb && !c->mrt && !c->prof; }
 
 // Steps whose force totals a launch (or a reader) forms: the launch before may
-// have taken two.
-int pending_steps(const lbm_ctx* c) { return c->L.pair ? 2 : 1; }
+// have taken two (not under interpolation, see lbm_set_boundary, nor with MRT).
+int pending_steps(const lbm_ctx* c) { return c->L.pair && !c->ibb && !c->mrt ? 2 : 1; }
 
 template <typename T>
 StepPtrs<T> step_ptrs(lbm_ctx* c) {
@@ -1098,8 +1098,12 @@ lbm_status lbm_set_boundary(lbm_ctx* c, int32_t rule) {
         set_err(c->err, "rule must be LBM_HALFWAY or LBM_INTERPOLATED");
         return LBM_EINVAL;
     }
+    // (the interpolated step forms the totals of one step before it; the last launch
+    // may have taken two)
+    if (c->L.pair && !c->ibb) finalize_pending(c);
     c->ibb = rule == LBM_INTERPOLATED ? 1 : 0;
     drop_graphs(c);
+    HIPCHK(c, hipGetLastError());
     return LBM_OK;
 }
 

@@ -19,6 +19,8 @@
 //              by a body at t+1 is written too and never read again)
 #pragma once
 
+#include <type_traits>
+
 #include "lbm_device.h"
 
 namespace lbm {
@@ -1012,12 +1014,9 @@ struct MoveShared {
     int nb_count;  // newborn nodes (part 1), links (part 0)
     int nb_list[kNewbornMax];
     int8_t nb_use[kNewbornBatch][8];  // -1: no participation, else 0/1/2
-    // (part 0: links per 64 box nodes, 16 bits each, over the same bytes)
-    union {
-        C nb_val[kNewbornBatch][8][3][9];
-        uint16_t group[kBoxGroups];
-    };
-    static_assert(sizeof(group) <= sizeof(nb_val), "the largest box's groups take no more LDS than the refill");
+    C nb_val[kNewbornBatch][8][3][9];  // (part 0: links per 64 box nodes, over the same bytes)
+    using Count = std::conditional_t<4 * kBoxGroups <= sizeof(nb_val), int, uint16_t>;
+    static_assert(sizeof(Count) * kBoxGroups <= sizeof(nb_val), "the largest box's groups");
     C nb_new[kNewbornBatch][9];
     C nb_mom[kNewbornBatch][4];
 };
@@ -1199,11 +1198,13 @@ __device__ inline void move_role(int m, uint8_t* __restrict__ lds, MoveShared<T>
     // links in the groups before, plus that of the lanes before in its own
     // (the ballots of the eight bits).  No thread walks a run of nodes: with a
     // contiguous run per thread this phase took 10 to 16 us of the mover's 13
-    // to 23 (discs of r = 9 to 15), now 4 to 5.  A count of links fits 16 bits:
-    // a node beside a convex body has at most three links into one of its sides,
-    // so the longest body whose box fits (a bar of 1 x 7,400 nodes) has 45,000.
+    // to 23 (discs of r = 9 to 15), now 4 to 5.  A count of links fits 16 bits
+    // (16-bit storage has no room for more): a node beside a convex body has at most
+    // three links into one of its sides, so the longest body whose box fits (a bar
+    // of 1 x 7,400 nodes) has 45,000.
     if (part == 0) {
-        uint16_t* gtot = sm.group;  // links per group, then before it
+        using Count = typename MoveShared<T>::Count;
+        Count* gtot = reinterpret_cast<Count*>(&sm.nb_val[0][0][0][0]);  // links per group, then before it
         const int lane = (int)threadIdx.x & 63;
         const int ngrp = (N + 63) / 64;
         {
@@ -1223,7 +1224,7 @@ __device__ inline void move_role(int m, uint8_t* __restrict__ lds, MoveShared<T>
                 int c = 0;
 #pragma unroll
                 for (int i = 0; i < 8; ++i) c += __builtin_popcountll(__ballot((bits >> i & 1u) != 0u));
-                if (lane == 0) gtot[q >> 6] = (uint16_t)c;
+                if (lane == 0) gtot[q >> 6] = (Count)c;
             }
         }
         __syncthreads();
@@ -1237,7 +1238,7 @@ __device__ inline void move_role(int m, uint8_t* __restrict__ lds, MoveShared<T>
                     const int y = __shfl_up(x, off, 64);
                     if (lane >= off) x += y;
                 }
-                if (g0 + lane < ngrp) gtot[g0 + lane] = (uint16_t)(carry + x - v);
+                if (g0 + lane < ngrp) gtot[g0 + lane] = (Count)(carry + x - v);
                 carry += __shfl(x, 63, 64);
             }
             if (lane == 0) sm.nb_count = carry;
@@ -1700,6 +1701,29 @@ __device__ inline void finalize_last(const StepPtrs<T>& p, int64_t t, int count,
     }
 }
 
+// The same, one step after the other and one load at a time: the interpolated and
+// the 16-bit kernels never follow a launch of two steps, and the code above costs
+// their longer roles more than it gives (64 steps of a free disc in 420 x 96: 1201 us
+// with it, 1168 so).
+template <typename T>
+__device__ inline void finalize_in_turn(const StepPtrs<T>& p, int64_t t, int count, const ForceArgs& a) {
+    for (int64_t u = t - count; u < t; ++u) {
+        if (u >= 0) {
+            const double* __restrict__ partial = p.part(u, a.nchunks);
+            const int* __restrict__ solid_chunk0 = p.solid_chunk0;
+            double* __restrict__ hist = p.hist;
+            const int64_t slot = u % a.hist_cap;
+            for (int r = threadIdx.x; r < a.nsol * 6; r += kBlock) {
+                const int sid = r / 6, q = r % 6;
+                double v = 0.0;
+                for (int cc = solid_chunk0[sid]; cc < solid_chunk0[sid + 1]; ++cc) v += partial[cc * 6 + q];
+                hist[(slot * a.nsol + sid) * 6 + q] = v;
+            }
+        }
+        __syncthreads();
+    }
+}
+
 // Finalize the forces of the last launch's steps (after the last launch of a
 // batch of steps).
 template <typename T>
@@ -1767,7 +1791,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(GEO ? 4 
         } else if (b == rc.n_force + rc.n_move) {
             // previous step's totals (its partials are complete: the
             // previous launch has ended); then advance the step counter
-            finalize_last(p, t, rc.n_fin, fa);
+            if constexpr (GEO || Sto<T>::kSplit)
+                finalize_in_turn(p, t, rc.n_fin, fa);
+            else
+                finalize_last(p, t, rc.n_fin, fa);
             if (threadIdx.x == 0) p.tctr[parity ^ 1] = t + 1;
         } else if constexpr (GEO) {
             const int c = b - (rc.n_force + rc.n_move + 1);

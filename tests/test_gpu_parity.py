@@ -738,3 +738,20 @@ def test_two_steps_in_one_launch_equal_two(lbm_mod, monkeypatch, dtype, nx, ny):
         b.step(n)
         assert bool((a.populations() == b.populations()).all()), (nx, ny, a.t)
         assert bool((a.force_history() == b.force_history()).all()), (nx, ny, a.t)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+def test_boundary_rule_changed_between_double_steps(lbm_mod, dtype):
+    """A lattice that takes two steps per launch, switched to interpolated
+    bounce-back and back after odd and even counts: fields and the forces of every
+    step equal those of single steps (the profiling mode)."""
+    c = _pair_case(2048, 1027, True, 5)
+    a, b, one = (lbm_mod.Lattice(c, dtype=dtype, history_steps=h) for h in (64, 64, 1))
+    b.profile(True)
+    for n, rule in ((2, True), (1, False), (4, True), (2, False), (3, True), (3, False), (35, False)):
+        for lat in (a, b, one):
+            lat.step(n)
+            lat.set_boundary(rule)
+        assert bool((a.populations() == b.populations()).all()), (a.t, rule)
+        assert bool((a.force_history() == b.force_history()).all()), (a.t, rule)
+        assert bool((one.force_history(one.t - 1, 1) == b.force_history(b.t - 1, 1)).all())
