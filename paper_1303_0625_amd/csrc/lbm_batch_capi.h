@@ -217,7 +217,7 @@ const char* batch_layout(const lbm_grid* grids, const double* taus, const lbm_so
     B.base = off;
     // two steps per launch: node flags, and the workgroup table (eight lists, each
     // at most one run longer than the shortest)
-    const bool pairs = es >= 4 && es * (size_t)pop_el >= kPairBytes && work.pays(grids[0].dtype);
+    const bool pairs = es >= 4 && es * (size_t)pop_el >= kPairBytes && work.pays(grids[0].dtype, false);
     B.n_ptiles_max = pairs ? (int)(8 * (units / 8 + most + 1)) : 0;
     take(B.o_flags, pairs ? (size_t)own_off : 0);
     take(B.o_ptiles, sizeof(PairTile) * (size_t)B.n_ptiles_max);
@@ -242,18 +242,25 @@ int build_tiles(lbm_batch* b, std::vector<Tile>& tiles, std::vector<int>& first,
 // Workgroups of the two-step update of the cases not yet converged.  The
 // hardware hands consecutive workgroups to the eight XCDs in turn: the runs of
 // rows go to eight lists, each next run to the shortest, so that the strips of a
-// run share an L2; the lists are interleaved and padded with empty entries.
+// run share an L2 (a run longer than a sixteenth of a list goes in pieces: four
+// cases of one run each would leave half the chip idle); the lists are interleaved
+// and padded with empty entries.
 void build_pair_tiles(lbm_batch* b, std::vector<PairTile>& tiles) {
     std::vector<PairTile> list[8];
+    int64_t units = 0;
+    for (int c = 0; c < b->n; ++c)
+        if (!b->conv_h[c]) units += (int64_t)b->cd[c].pair.strips * b->cd[c].pair.runs;
+    const int piece = (int)std::max<int64_t>(1, units / (8 * 16));
     for (int c = 0; c < b->n; ++c) {
         if (b->conv_h[c]) continue;
         const PairArgs& a = b->cd[c].pair;
-        for (int r = 0; r < a.runs; ++r) {
-            int k = 0;
-            for (int j = 1; j < 8; ++j)
-                if (list[j].size() < list[k].size()) k = j;
-            for (int s = 0; s < a.strips; ++s) list[k].push_back(PairTile{c, s, r, 0});
-        }
+        for (int r = 0; r < a.runs; ++r)
+            for (int s0 = 0; s0 < a.strips; s0 += piece) {
+                int k = 0;
+                for (int j = 1; j < 8; ++j)
+                    if (list[j].size() < list[k].size()) k = j;
+                for (int s = s0; s < std::min(s0 + piece, a.strips); ++s) list[k].push_back(PairTile{c, s, r, 0});
+            }
     }
     size_t n = 0;
     for (const auto& l : list) n = std::max(n, l.size());

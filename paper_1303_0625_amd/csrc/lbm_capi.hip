@@ -84,14 +84,20 @@ constexpr size_t kPairBytes = 64ull << 20;
 // one / two: FP32 batches of 64 x 64 cases (0.25) 82 / 62 us, 128 x 64 (0.33) 68 /
 // 62, 320 x 24 (0.357) 27.0 / 25.6, 128 x 96 (0.364) 24.7 / 25.1, 192 x 64 (0.38)
 // 24.7 / 25.4, 56 x 96 (0.55) 35 / 62; FP64, bound by its bytes sooner: 64 x 24 (0.21)
-// 167 / 150, 64 x 64 (0.25) 62.9 / 61.2, 120 x 24 (0.29) 25.5 / 25.8.
+// 167 / 150, 64 x 64 (0.25) 62.9 / 61.2, 120 x 24 (0.29) 25.5 / 25.8.  A single
+// lattice that streams from HBM is bound by its bytes sooner still: FP32 1,000,000 x
+// 4 (0.175) 59 / 55, 4,000,000 x 5 (0.21) 253 / 274, 64 x 60,000 (0.28) 44 / 50; FP64
+// 1,000,000 x 4 80 / 112.
 struct PairWork {
     double one = 0.0, two = 0.0;
     void add(int nx, int ny, const PairArgs& a) {
         one += (double)((nx + 63) / 64) * ny;
         two += (double)a.strips * (ny + 16.0 * a.runs);
     }
-    bool pays(int dtype) const { return one >= (dtype == LBM_F64 ? 0.26 : 0.36) * two; }
+    bool pays(int dtype, bool streams) const {
+        const double least = dtype == LBM_F64 ? (streams ? 0.17 : 0.26) : (streams ? 0.2 : 0.36);
+        return one >= least * two;
+    }
 };
 
 // Workspace layout (byte offsets inside the caller's buffer).
@@ -165,7 +171,7 @@ bool make_layout(const lbm_grid& g, const lbm_solid* solids, int n, int64_t hist
     for (int k = 0; k < n; ++k) L.n_movers += solids[k].moves ? 1 : 0;
     PairWork work;
     work.add(g.nx, g.ny, pair_args(g.nx, g.ny));
-    L.pair = L.n_movers == 0 && es >= 4 && fbytes >= kPairBytes && work.pays(g.dtype);
+    L.pair = L.n_movers == 0 && es >= 4 && fbytes >= kPairBytes && work.pays(g.dtype, 2 * fbytes > kStreamBytes);
     for (int k = 0; k < 2; ++k) {
         L.own[k] = off;
         off = align256(off + (size_t)g.ny * L.opitch);
@@ -475,7 +481,8 @@ lbm_status enqueue_pair(lbm_ctx* c) {
     rc.n_move = 0;
     rc.n_fin = 2;
     rc.n_lead = (2 * rc.n_force + 1 + 7) / 8 * 8;
-    k_pair<T><<<(unsigned)(rc.n_lead + pa.strips * ((pa.runs + 7) / 8 * 8)), kBlock, 0, c->stream>>>(
+    const int64_t units = (int64_t)pa.strips * (pa.runs / 8 * 8) + ((int64_t)pa.strips * (pa.runs % 8) + 7) / 8 * 8;
+    k_pair<T><<<(unsigned)(rc.n_lead + units), kBlock, 0, c->stream>>>(
         sp, wsp<uint8_t>(c, c->L.own[1]), c->cur, rc, step_args(c), force_args(c), pa, collide_params<C>(c));
     c->t += 2;
     c->cur ^= 1;

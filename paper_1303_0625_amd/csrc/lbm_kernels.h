@@ -2195,12 +2195,24 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T
         return;
     }
     // XCD k = j % 8 takes the runs k, k + 8, ...: neighbouring strips of a run
-    // share an L2, and the eight XCDs stay in one neighbourhood of rows
-    const uint32_t j = (uint32_t)(b - rc.n_lead), q = j >> 3;
-    const uint32_t group = q / (uint32_t)pa.strips;
-    const int run = (int)(group * 8u + (j & 7u)), strip = (int)(q - group * (uint32_t)pa.strips);
-    if (run >= pa.runs) return;
-    const int x0 = strip * pa.width;
+    // share an L2, and the eight XCDs stay in one neighbourhood of rows.  The runs
+    // left over, fewer than eight, are cut into eight pieces, one per XCD (a
+    // lattice of 300,000 x 16 has one run: 48 us per step, on one XCD 256)
+    const uint32_t j = (uint32_t)(b - rc.n_lead), q = j >> 3, strips = (uint32_t)pa.strips;
+    const uint32_t whole = (uint32_t)pa.runs >> 3, rest = ((uint32_t)pa.runs & 7u) * strips;
+    uint32_t run, strip;
+    if (q < whole * strips) {
+        const uint32_t group = q / strips;
+        run = group * 8u + (j & 7u);
+        strip = q - group * strips;
+    } else {
+        const uint32_t piece = (rest + 7u) >> 3, unit = (j & 7u) * piece + (q - whole * strips);
+        if (unit >= rest) return;
+        run = unit / strips;
+        strip = unit - run * strips;
+        run += whole * 8u;
+    }
+    const int x0 = (int)strip * pa.width;
     const int nout = x0 + pa.width <= sa.nx ? pa.width : sa.nx - x0;
     const int Ya = (int)((int64_t)sa.ny * run / pa.runs), Yb = (int)((int64_t)sa.ny * (run + 1) / pa.runs);
     pair_strip<T>(sh.s, p.fin, p.fout, p.own_t, flags, p.vtab, x0, nout, Ya, Yb, sa, cp);

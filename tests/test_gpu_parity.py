@@ -696,7 +696,10 @@ def test_force_totals_of_short_histories(lbm_mod, dtype, nx, ny):
     (64, 29200, "f32", {}, 1),
     (64, 14600, "f64", {}, 2),                    # (bound by its bytes sooner)
     (113, 15007, "f32", {}, 2),                   # three strips, two waves
-    (4200000, 4, "f64", {}, 1),                   # runs of four rows
+    (57, 60000, "f32", {}, 2),                    # the same, streamed from HBM
+    (1000000, 4, "f32", {}, 1),                   # runs of four rows
+    (1000000, 4, "f64", {}, 2),
+    (300000, 16, "f32", {}, 2),                   # one run
     (2048, 1024, "f32", {"mrt": (1.64, 1.54, 1.9)}, 1),
     (2048, 1024, "f32", {"ibb": True}, 1),
     (2048, 1024, "f32", {"moves": True}, 1),
@@ -720,7 +723,9 @@ def test_which_lattices_take_two_steps_per_launch(lbm_mod, monkeypatch, nx, ny, 
 
 
 @pytest.mark.parametrize("dtype,nx,ny", [("f64", 64, 14600), ("f64", 57, 14600), ("f64", 128, 7400), ("f32", 113, 15007),
-                                         ("f32", 56, 29201), ("f32", 65, 14601), ("f32", 2048, 1027)])
+                                         ("f32", 56, 29201), ("f32", 65, 14601), ("f32", 2048, 1027), ("f32", 57, 60000),
+                                         # four runs of rows, and nine, in pieces for the eight parts of the chip
+                                         ("f32", 50003, 61), ("f64", 9001, 171)])
 def test_two_steps_in_one_launch_equal_two(lbm_mod, monkeypatch, dtype, nx, ny):
     """Lattices seen to take two steps per launch equal single steps (the
     profiling mode) bit for bit, populations and forces."""
