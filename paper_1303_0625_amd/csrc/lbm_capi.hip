@@ -463,7 +463,7 @@ StepPtrs<T> step_ptrs(lbm_ctx* c) {
     sp.partial = wsp<double>(c, c->L.partial);
     // (a chunk's 96 bytes fit its share of the link capacity: a body's is at
     // least 128 links, the walls' 6 nx, and an empty list still has 256 bytes)
-    sp.partial_b = c->L.pair ? wsp<double>(c, c->L.links[1]) : sp.partial;
+    sp.partial_gap = c->L.pair ? wsp<double>(c, c->L.links[1]) - sp.partial : 0;
     sp.hist = wsp<double>(c, c->L.hist);
     sp.tctr = wsp<int64_t>(c, c->L.tctr);
     sp.errflag = wsp<int>(c, c->L.err);

@@ -126,7 +126,7 @@ struct CollideParams {
     // [0] and diagonal [1] directions
     C keep, hgx, hgy, p3, p9[2], p3w[2], w3[2], w45[2];
 };
-inline void fill_products(CollideParams<double>& p) {
+__host__ __device__ inline void fill_products(CollideParams<double>& p) {
     p.keep = 1.0 - p.omega;
     p.hgx = 0.5 * p.gx;
     p.hgy = 0.5 * p.gy;
@@ -139,7 +139,7 @@ inline void fill_products(CollideParams<double>& p) {
         p.w45[k] = 4.5 * w;
     }
 }
-inline void fill_products(CollideParams<float>&) {}
+__host__ __device__ inline void fill_products(CollideParams<float>&) {}
 
 // 1/x: a correctly rounded division in FP64; in FP32, the arithmetic of the
 // 16-bit storages, the hardware reciprocal (within 1 ulp, far below the

@@ -1660,13 +1660,13 @@ struct StepPtrs {
     const double* vtab;
     const double* rtab;  // rotation table of this step
     const int* movers;
-    double* partial;    // [2][nchunks][6]: steps u with (u & 2) == 0, by parity
-    double* partial_b;  // the same for (u & 2) != 0 (translating bodies: `partial` again)
+    double* partial;      // [2][nchunks][6]: steps u with (u & 2) == 0, by parity
+    int64_t partial_gap;  // elements from there to the same for (u & 2) != 0 (0: `partial` again)
     double* hist;
     int64_t* tctr;      // step counter, slot toggled by every launch
     int* errflag;
     __device__ inline double* part(int64_t u, int nchunks) const {
-        return ((u & 2) != 0 ? partial_b : partial) + (size_t)(u & 1) * nchunks * 6;
+        return partial + (u & 1) * (int64_t)(nchunks * 6) + (u >> 1 & 1) * partial_gap;
     }
 };
 
@@ -1701,25 +1701,30 @@ __device__ inline void finalize_last(const StepPtrs<T>& p, int64_t t, int count,
     }
 }
 
-// The same, one step after the other and one load at a time: the interpolated and
-// the 16-bit kernels never follow a launch of two steps, and the code above costs
-// their longer roles more than it gives (64 steps of a free disc in 420 x 96: 1201 us
-// with it, 1168 so).
+// The same of one step u, one load at a time: the interpolated kernels never follow
+// a launch of two steps, and the code above costs their longer roles more than it
+// gives (64 steps of a free disc in 420 x 96: 1201 us with it, 1143 so; interpolated
+// FP32 channel of 1024 x 512 with fixed discs: 14.4, 13.0 us per step).
+template <typename T>
+__device__ inline void finalize_step(const StepPtrs<T>& p, int64_t u, const ForceArgs& a) {
+    if (u < 0) return;
+    const double* __restrict__ partial = p.part(u, a.nchunks);
+    const int64_t slot = u % a.hist_cap;
+    for (int r = threadIdx.x; r < a.nsol * 6; r += kBlock) {
+        const int sid = r / 6, q = r % 6;
+        double v = 0.0;
+        for (int cc = p.solid_chunk0[sid]; cc < p.solid_chunk0[sid + 1]; ++cc) v += partial[cc * 6 + q];
+        p.hist[(slot * a.nsol + sid) * 6 + q] = v;
+    }
+}
+
+// The same of the steps before t, in turn: the 16-bit kernels, where either of the
+// above costs the mover 2 to 3% (64 steps of 1000 x 500 with five translating discs:
+// 864 us, 835 so).
 template <typename T>
 __device__ inline void finalize_in_turn(const StepPtrs<T>& p, int64_t t, int count, const ForceArgs& a) {
     for (int64_t u = t - count; u < t; ++u) {
-        if (u >= 0) {
-            const double* __restrict__ partial = p.part(u, a.nchunks);
-            const int* __restrict__ solid_chunk0 = p.solid_chunk0;
-            double* __restrict__ hist = p.hist;
-            const int64_t slot = u % a.hist_cap;
-            for (int r = threadIdx.x; r < a.nsol * 6; r += kBlock) {
-                const int sid = r / 6, q = r % 6;
-                double v = 0.0;
-                for (int cc = solid_chunk0[sid]; cc < solid_chunk0[sid + 1]; ++cc) v += partial[cc * 6 + q];
-                hist[(slot * a.nsol + sid) * 6 + q] = v;
-            }
-        }
+        finalize_step(p, u, a);
         __syncthreads();
     }
 }
@@ -1773,6 +1778,11 @@ template <typename T, bool NT, bool MRT, bool GEO>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(GEO ? 4 : (Sto<T>::kSplit ? 6 : 8), 8))) void k_fused(
     StepPtrs<T> p, int parity, RoleCounts rc, StepArgs sa, MoveArgs ma, ForceArgs fa,
     CollideParams<typename Sto<T>::C> cp) {
+    // (the interpolated kernel forms the collision's products: read as arguments
+    // behind its long boundary code they cost another round trip, FP64 channel of 1024
+    // x 512 with fixed discs 19.3 us per step read, 18.4 formed; the half-way kernel
+    // is 4% faster with them read)
+    if constexpr (GEO) fill_products(cp);
     extern __shared__ __align__(16) uint8_t dyn_lds[];
     __shared__ union Shared {
         ForceShared f;
@@ -1791,7 +1801,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(GEO ? 4 
         } else if (b == rc.n_force + rc.n_move) {
             // previous step's totals (its partials are complete: the
             // previous launch has ended); then advance the step counter
-            if constexpr (GEO || Sto<T>::kSplit)
+            if constexpr (GEO)
+                finalize_step(p, t - 1, fa);
+            else if constexpr (Sto<T>::kSplit)
                 finalize_in_turn(p, t, rc.n_fin, fa);
             else
                 finalize_last(p, t, rc.n_fin, fa);
