@@ -651,9 +651,6 @@ lbm_status lbm_batch_create(const lbm_grid* grids, const double* taus, const lbm
         const int nb = d.nsol - 1;
         const SolidDev* sd = bws<SolidDev>(b, b->o_sol) + d.solid_base;
         if (nb > 0) k_raster<<<nb, kBlock, 0, st>>>(own, sd, bws<int>(b, b->o_list), 0, ga);
-        if (b->pairs)
-            k_node_flags<<<(unsigned)(((int64_t)g.ny * d.sa.rowlen + kBlock - 1) / kBlock), kBlock, 0, st>>>(
-                own, bws<uint8_t>(b, b->o_flags) + d.own_off, d.sa);
         uint32_t* L = bws<uint32_t>(b, b->o_links) + d.links_base;
         if (g.walls_y) k_wall_links<<<(2 * g.nx + 255) / 256, 256, 0, st>>>(L, g.nx, g.ny);
         if (nb > 0) {
@@ -664,6 +661,11 @@ lbm_status lbm_batch_create(const lbm_grid* grids, const double* taus, const lbm
                                            0, la, bws<int>(b, b->o_err));
         }
         if (e == hipSuccess) e = hipGetLastError();
+    }
+    if (b->pairs && e == hipSuccess) {
+        k_batch_node_flags<<<dim3(64, (unsigned)std::min(n_cases, 65535)), kBlock, 0, st>>>(
+            bws<CaseDev>(b, b->o_cases), n_cases, bws<uint8_t>(b, b->o_own), bws<uint8_t>(b, b->o_flags));
+        e = hipGetLastError();
     }
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e != hipSuccess) {

@@ -79,6 +79,19 @@ __global__ __launch_bounds__(WAVES * 64) void k_batch_step(const CaseDev* __rest
                      vtab_all + 2 * cd.solid_base, nullptr, nullptr, 0, sa, cp, nullptr, x < sa.nx);
 }
 
+// Node flags of every case, in one launch (a launch per case added 8 us each to a
+// batch's creation).
+__global__ __launch_bounds__(kBlock) void k_batch_node_flags(const CaseDev* __restrict__ cases, int n_cases,
+                                                             const uint8_t* __restrict__ obase,
+                                                             uint8_t* __restrict__ flags) {
+    for (int c = (int)blockIdx.y; c < n_cases; c += (int)gridDim.y) {
+        const CaseDev& cd = cases[c];
+        const int64_t words = (int64_t)cd.sa.ny * cd.sa.rowlen / 8;
+        for (int64_t w = (int64_t)blockIdx.x * kBlock + threadIdx.x; w < words; w += (int64_t)gridDim.x * kBlock)
+            node_flags_word(obase + cd.own_off, flags + cd.own_off, cd.sa, w);
+    }
+}
+
 // Two time steps of every listed workgroup of the two-step update (strip and run
 // of a case; c < 0: none); a case marked converged is skipped.  slot: the buffer
 // read, toggled by every launch, as is the slot of the step counter.

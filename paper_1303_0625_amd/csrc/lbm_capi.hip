@@ -496,7 +496,7 @@ lbm_status dispatch_pair(lbm_ctx* c) {
 // Node flags of a lattice that may take two steps per launch, from its owner map.
 void enqueue_flags(lbm_ctx* c) {
     if (!c->L.pair) return;
-    k_node_flags<<<(unsigned)node_blocks(c), kBlock, 0, c->stream>>>(own_ptr(c, 0), wsp<uint8_t>(c, c->L.own[1]),
+    k_node_flags<<<(unsigned)((node_blocks(c) + 7) / 8), kBlock, 0, c->stream>>>(own_ptr(c, 0), wsp<uint8_t>(c, c->L.own[1]),
                                                                      step_args(c));
 }
 
