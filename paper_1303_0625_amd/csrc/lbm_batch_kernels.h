@@ -65,8 +65,11 @@ __global__ __launch_bounds__(WAVES * 64) void k_batch_step(const CaseDev* __rest
     const CaseDev& cd = cases[tl.c];
     // (copies: read together, beside the populations' loads, and not again after
     // every store; read where they are used they cost three round trips in a row,
-    // 26.4 us per step of 72 MiB of FP32 cases against 25.6, FP16 75 against 38)
-    const CollideParams<typename Sto<T>::C> cp = case_cp<T>(cd);
+    // 26.4 us per step of 72 MiB of FP32 cases against 25.6, FP16 75 against 38.  The
+    // 16-bit collision keeps its reference: a copy changes which of its products the
+    // compiler fuses, and so the last bits of every result)
+    using CP = CollideParams<typename Sto<T>::C>;
+    std::conditional_t<Sto<T>::kSplit, const CP&, const CP> cp = case_cp<T>(cd);
     const StepArgs sa = cd.sa;
     const int w = tl.wave0 + (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (w >= cd.nwaves) return;
