@@ -531,7 +531,10 @@ lbm_status enqueue_step(lbm_ctx* c) {
     using KF = decltype(&k_fused<T, true, true, true>);
     KF kern;
     // per-link surface geometry: spinning free bodies or interpolated bounce-back
-    if (n_free > 0 || c->ibb)
+    if ((n_free > 0 || c->ibb) && n_presc == 0)
+        kern = c->mrt ? (nt ? k_fused<T, true, true, true, false> : k_fused<T, false, true, true, false>)
+                      : (nt ? k_fused<T, true, false, true, false> : k_fused<T, false, false, true, false>);
+    else if (n_free > 0 || c->ibb)
         kern = c->mrt ? (nt ? k_fused<T, true, true, true> : k_fused<T, false, true, true>)
                       : (nt ? k_fused<T, true, false, true> : k_fused<T, false, false, true>);
     else

@@ -1718,9 +1718,9 @@ __device__ inline void finalize_step(const StepPtrs<T>& p, int64_t u, const Forc
     }
 }
 
-// The same of the steps before t, in turn: the 16-bit kernels, where either of the
-// above costs the mover 2 to 3% (64 steps of 1000 x 500 with five translating discs:
-// 864 us, 835 so).
+// The same of the steps before t, in turn: the 16-bit kernels, and the interpolated
+// MRT kernel with movers, where either of the above costs the mover 1 to 3% (64 steps
+// of 1000 x 500 FP16 with five translating discs: 864 us, 837 so).
 template <typename T>
 __device__ inline void finalize_in_turn(const StepPtrs<T>& p, int64_t t, int count, const ForceArgs& a) {
     for (int64_t u = t - count; u < t; ++u) {
@@ -1774,7 +1774,10 @@ __device__ inline void boundary_role(int wg, const StepPtrs<T>& p, int64_t t, co
 // update at full occupancy; the geometry variant allows 128 (4 waves), since
 // its boundary and refill roles would otherwise spill, and spill traffic
 // lengthens their dependent chains under the update's saturated HBM.
-template <typename T, bool NT, bool MRT, bool GEO>
+// MOVE: prescribed bodies may translate; interpolated lattices without one take a
+// kernel without the mover's role (FP32 MRT channel of 1024 x 512 with fixed discs
+// 14.2 us per step with it, 13.4 without; FP16 2048 x 2048 41.8, 39.2).
+template <typename T, bool NT, bool MRT, bool GEO, bool MOVE = true>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(GEO ? 4 : (Sto<T>::kSplit ? 6 : 8), 8))) void k_fused(
     StepPtrs<T> p, int parity, RoleCounts rc, StepArgs sa, MoveArgs ma, ForceArgs fa,
     CollideParams<typename Sto<T>::C> cp) {
@@ -1795,15 +1798,16 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(GEO ? 4 
             force_role<T, GEO>(b, sh.f, p.fin, p.own_t, p.links_t, p.seg_cnt_t, p.seg_off, p.chunk_solid, p.chunk_start,
                           p.sol, p.vtab, p.rtab, p.part(t, fa.nchunks), t, fa);
         } else if (b < rc.n_force + rc.n_move) {
-            move_role<T, MRT, GEO>(b - rc.n_force, dyn_lds, sh.m, p.fin, p.fout, p.own_t, p.own_n, p.links_n,
-                         p.seg_cnt_n, p.seg_off, p.seg_cap, p.sol, p.vtab, p.rtab, p.movers, p.tctr, parity,
-                         ma, cp, p.errflag);
+            if constexpr (MOVE)
+                move_role<T, MRT, GEO>(b - rc.n_force, dyn_lds, sh.m, p.fin, p.fout, p.own_t, p.own_n, p.links_n,
+                                       p.seg_cnt_n, p.seg_off, p.seg_cap, p.sol, p.vtab, p.rtab, p.movers, p.tctr,
+                                       parity, ma, cp, p.errflag);
         } else if (b == rc.n_force + rc.n_move) {
             // previous step's totals (its partials are complete: the
             // previous launch has ended); then advance the step counter
-            if constexpr (GEO)
+            if constexpr (GEO && !(MRT && MOVE))
                 finalize_step(p, t - 1, fa);
-            else if constexpr (Sto<T>::kSplit)
+            else if constexpr (Sto<T>::kSplit || GEO)
                 finalize_in_turn(p, t, rc.n_fin, fa);
             else
                 finalize_last(p, t, rc.n_fin, fa);
