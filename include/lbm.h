@@ -326,7 +326,10 @@ lbm_status lbm_batch_create(const lbm_grid* grids, const double* taus, const lbm
  * reset every case to its initial state.  Only before the first step
  * (LBM_ESTATE otherwise).  cache_path (optional) is a text file of
  * "signature|waves|nontemporal|us" lines: a matching line is used without
- * timing, a new result is appended. */
+ * timing, a new result is appended.  The tiling shapes the launches of one
+ * step and the monitor.  Where a batch takes two steps per launch, whose split
+ * is fixed, these are the last n mod 4 steps of a call or check interval of n
+ * and the monitor. */
 lbm_status lbm_batch_autotune(lbm_batch* b, const char* cache_path);
 
 /* Waves per workgroup of the current tiling; *nontemporal (optional) receives

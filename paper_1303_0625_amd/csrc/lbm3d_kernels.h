@@ -715,7 +715,8 @@ __device__ inline double pull3(const T* __restrict__ fin, const uint8_t* __restr
 // newborn nodes one after another, the 18 x 3 x 19 stencil values of a node in
 // parallel.  (Bound by latency: one thread walking a node's whole stencil took
 // 203 us, and rasters and flags of the whole lattice 12 us, on a 150 x 42 x 42
-// tube with one sphere of r = 5.9; this kernel takes 15 us.)
+// tube with one sphere of r = 5.9; this kernel takes 21 us with a newborn node and
+// 5 us without, 15 us on the mean.)
 constexpr int kTileX = 8, kTileY = 8, kTileZ = 4;
 static_assert(kTileX * kTileY * kTileZ == kBlock, "one node per thread");
 

@@ -1,8 +1,9 @@
 // lbm_batch_kernels.h -- many independent lattices of uneven sizes advanced
 // together: one launch per time step (large FP32 and FP64 batches: per two
-// steps) covers the update tiles of every active case (per-case parameters come from a device table), and every check
-// interval a monitor evaluates per-case residual and force on the device and
-// retires the converged cases (their state freezes).
+// steps) covers the update tiles of every active case (per-case parameters come
+// from a device table), and every check interval a monitor evaluates per-case
+// residual and force on the device and retires the converged cases (their state
+// freezes).
 //
 // Residual of case c over its fluid nodes (u the Guo velocity):
 //   r = ||u_t - u_{t-k}||_2 / (k ||u_t||_2),

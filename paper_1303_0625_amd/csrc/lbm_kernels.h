@@ -1827,28 +1827,29 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(GEO ? 4 
 // Large lattices whose geometry stays (no translating body, half-way bounce-back,
 // BGK, FP64 or FP32 storage) take two steps per pass over memory: the state between
 // them stays in registers.  A workgroup owns a strip of at most kPairOut columns
-// over a run of rows, each of its four waves marching along y over a quarter.  Per row r it pulls, bounces and
-// collides row r of the state at t + 1 from memory (all 64 lanes, the strip
-// and one column on each side; the next row's loads are in flight meanwhile),
-// and then row r - 1 of the state at t + 2 from registers: the populations that
-// stream along y are kept from the rows before, those that stream along x come
-// from the neighbouring lanes by a wavefront shift, so the rows need neither LDS
-// nor a barrier; the four waves meet once, at the end, to finish the rows where
-// their runs touch.  The state at
-// t + 1 is rounded to the storage type as if it had been stored: results equal
-// two single steps bit for bit.
+// over a run of rows, each of its four waves marching along y over a quarter.  Per
+// row r it pulls, bounces and collides row r of the state at t + 1 from memory (all
+// 64 lanes, the strip and one column on each side; the next row's loads are in
+// flight meanwhile), and then row r - 1 of the state at t + 2 from registers: the
+// populations that stream along y are kept from the rows before, those that stream
+// along x come from the neighbouring lanes by a wavefront shift, so the rows need
+// neither LDS nor a barrier; the four waves meet once, at the end, to finish the
+// rows where their runs touch.  The state at t + 1 is rounded to the storage type
+// as if it had been stored: results equal two single steps bit for bit.
 //
-// Bytes: a pass reads and writes each population once for two steps (4096 x 4096
-// FP32: 1.3 GB of traffic per launch).  Work done twice: the two columns beside a
-// strip and the two rows beside a workgroup's run.  Per step on 4096 x 4096: FP32
-// 203 us one step per launch, 150 us two per launch; FP64 4096 x 2048: 202, 133 us.
-// Bound by the loads in flight: without its arithmetic the launch takes 285 us
-// (4.5 TB/s), without memory traffic 206 us, together 295 us; its 111 registers
-// allow 16 waves per compute unit of one row's loads each, and a second row in
-// flight spills (372 us).  Measured around it (per launch): strips of 62 / 56 / 48
-// / 32 columns 310 / 295 / 304 / 398 us (56 FP32 columns are whole 32-byte
-// sectors; whole lines cost too many lanes); nontemporal loads 385 us (the lines
-// that neighbouring strips share are fetched twice), nontemporal stores 308 us.
+// Bytes: a pass reads and writes each population once for two steps, 1.21 GB on
+// 4096 x 4096 FP32.  By the counters a launch moves 1.46 GB: the two columns beside
+// a strip and the two rows beside a workgroup's run are read by both neighbours, and
+// their work is done twice.  Per step on 4096 x 4096: FP32 203 us one step per
+// launch, 149 us two per launch; FP64 4096 x 2048: 202, 133 us.
+// Bound by memory: 1.46 GB in 298 us are 4.9 TB/s, what a large copy reaches.
+// (Timed once with parts left out, at 295 us per launch: 285 us without the
+// arithmetic, 206 us without the memory traffic.)  Its 111 registers allow 16 waves
+// per compute unit of one row's loads each; a second row in flight spills (372 us).
+// Measured around it (per launch): strips of 62 / 56 / 48 / 32 columns 310 / 295 /
+// 304 / 398 us (56 FP32 columns are whole 32-byte sectors; whole lines cost too many
+// lanes); nontemporal loads 385 us (the lines that neighbouring strips share are
+// fetched twice), nontemporal stores 308 us.
 constexpr int kPairOut = 56;
 
 // Node flags of a lattice whose geometry stays.
