@@ -1838,11 +1838,11 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(GEO ? 4 
 // as if it had been stored: results equal two single steps bit for bit.
 //
 // Bytes: a pass reads and writes each population once for two steps, 1.21 GB on
-// 4096 x 4096 FP32.  By the counters a launch moves 1.46 GB: the two columns beside
+// 4096 x 4096 FP32.  By the counters a launch moves 1.45 GB: the two columns beside
 // a strip and the two rows beside a workgroup's run are read by both neighbours, and
 // their work is done twice.  Per step on 4096 x 4096: FP32 203 us one step per
 // launch, 149 us two per launch; FP64 4096 x 2048: 202, 133 us.
-// Bound by memory: 1.46 GB in 298 us are 4.9 TB/s, what a large copy reaches.
+// Bound by memory: 1.45 GB in 298 us are 4.9 TB/s, what a large copy reaches.
 // (Timed once with parts left out, at 295 us per launch: 285 us without the
 // arithmetic, 206 us without the memory traffic.)  Its 111 registers allow 16 waves
 // per compute unit of one row's loads each; a second row in flight spills (372 us).
